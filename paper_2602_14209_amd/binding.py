@@ -1,10 +1,14 @@
-"""Thin ctypes binding of libmage.so (argument marshalling only).
+"""Thin binding of libmage.so (argument marshalling only).
 
 Every step of the MAGE hot path runs inside the HIP library; PyTorch is used for
 device memory and streams.  The functions carry the names of the C entry points
 declared in ``include/mage.h`` and take torch CUDA(HIP) tensors in place of raw
 device pointers.  There is no CPU fallback: if the library is missing, importing
 or calling this module raises.
+
+The calls of the hot path are marshalled by ``_marshal`` (csrc/marshal.cpp): a denoising step
+takes 6 us on the GPU, less than ctypes and torch's Python API need to look at its arguments.  The
+measurement aids and the size queries go through ctypes.
 """
 from __future__ import annotations
 
@@ -41,6 +45,20 @@ class MageError(RuntimeError):
 
 
 _lib = None
+
+
+class _LoadMarshal:
+    """Stands in for the marshalling module until the first call (which raises if it is not built)."""
+
+    def __getattr__(self, name):
+        global _m
+        lib()
+        from . import _marshal
+        _m = _marshal
+        return getattr(_marshal, name)
+
+
+_m = _LoadMarshal()
 
 
 def lib() -> ctypes.CDLL:
@@ -147,63 +165,51 @@ def _wsize(ws: Optional[torch.Tensor]) -> int:
 
 def mage_select(shape: mage_shape, q1, k_cache, idx_out, alpha_out, workspace, stream=None) -> int:
     """Step-1 selection; see include/mage.h.  Returns the status code (0 = ok)."""
-    return lib().mage_select(ctypes.byref(shape), _ptr(q1), _ptr(k_cache), _ptr(idx_out), _ptr(alpha_out),
-                             _ptr(workspace), _wsize(workspace), _stream(stream))
+    return _m.select(shape, q1, k_cache, idx_out, alpha_out, workspace, stream)
 
 
 def mage_block_probs(shape: mage_shape, q1, k_cache, pbar_out, workspace, stream=None) -> int:
     """Block-averaged probabilities per query head, pbar_out [Hq,L]; see include/mage.h."""
-    return lib().mage_block_probs(ctypes.byref(shape), _ptr(q1), _ptr(k_cache), _ptr(pbar_out),
-                                  _ptr(workspace), _wsize(workspace), _stream(stream))
+    return _m.block_probs(shape, q1, k_cache, pbar_out, workspace, stream)
 
 
 def mage_exact_attn(shape: mage_shape, q, k_cache, v_cache, k_blk, v_blk, out, lse_out, workspace, stream=None) -> int:
     """Exact attention over cache + block; see include/mage.h."""
-    return lib().mage_exact_attn(ctypes.byref(shape), _ptr(q), _ptr(k_cache), _ptr(v_cache), _ptr(k_blk), _ptr(v_blk),
-                                 _ptr(out), _ptr(lse_out), _ptr(workspace), _wsize(workspace), _stream(stream))
+    return _m.exact_attn(shape, q, k_cache, v_cache, k_blk, v_blk, out, lse_out, workspace, stream)
 
 
 def mage_sparse_attn(shape: mage_shape, q, k_cache, v_cache, idx, k_blk, v_blk, out, lse_out, workspace,
                      stream=None) -> int:
     """Sparse attention of one denoising step; see include/mage.h."""
-    return lib().mage_sparse_attn(ctypes.byref(shape), _ptr(q), _ptr(k_cache), _ptr(v_cache), _ptr(idx), _ptr(k_blk),
-                                  _ptr(v_blk), _ptr(out), _ptr(lse_out), _ptr(workspace), _wsize(workspace),
-                                  _stream(stream))
+    return _m.sparse_attn(shape, q, k_cache, v_cache, idx, k_blk, v_blk, out, lse_out, workspace, stream)
 
 
 def mage_step1(shape: mage_shape, q1, k_cache, v_cache, k_blk, v_blk, out, lse_out, idx_out, alpha_out, workspace,
                stream=None) -> int:
     """Step-1 attention and selection in one call (shared statistics pass); see include/mage.h."""
-    return lib().mage_step1(ctypes.byref(shape), _ptr(q1), _ptr(k_cache), _ptr(v_cache), _ptr(k_blk), _ptr(v_blk),
-                            _ptr(out), _ptr(lse_out), _ptr(idx_out), _ptr(alpha_out), _ptr(workspace),
-                            _wsize(workspace), _stream(stream))
+    return _m.step1(shape, q1, k_cache, v_cache, k_blk, v_blk, out, lse_out, idx_out, alpha_out, workspace, stream)
 
 
 def mage_compact(shape: mage_shape, k_cache, v_cache, idx, k_sel, v_sel, stream=None) -> int:
     """Copy the selected rows into a cache of length k; see include/mage.h."""
-    return lib().mage_compact(ctypes.byref(shape), _ptr(k_cache), _ptr(v_cache), _ptr(idx), _ptr(k_sel), _ptr(v_sel),
-                              _stream(stream))
+    return _m.compact(shape, k_cache, v_cache, idx, k_sel, v_sel, stream)
 
 
 def mage_sparse_attn_compact(shape: mage_shape, q, k_sel, v_sel, k_blk, v_blk, out, lse_out, workspace,
                              stream=None) -> int:
     """Sparse step on compacted rows; see include/mage.h."""
-    return lib().mage_sparse_attn_compact(ctypes.byref(shape), _ptr(q), _ptr(k_sel), _ptr(v_sel), _ptr(k_blk),
-                                          _ptr(v_blk), _ptr(out), _ptr(lse_out), _ptr(workspace), _wsize(workspace),
-                                          _stream(stream))
+    return _m.sparse_attn_compact(shape, q, k_sel, v_sel, k_blk, v_blk, out, lse_out, workspace, stream)
 
 
 def mage_sparse_attn_batched(shape: mage_shape, n_seq: int, q, k_cache, v_cache, idx, k_blk, v_blk, out, lse_out,
                              stream=None) -> int:
     """Sparse step of n_seq independent sequences in one launch; see include/mage.h."""
-    return lib().mage_sparse_attn_batched(ctypes.byref(shape), int(n_seq), _ptr(q), _ptr(k_cache), _ptr(v_cache),
-                                          _ptr(idx), _ptr(k_blk), _ptr(v_blk), _ptr(out), _ptr(lse_out),
-                                          _stream(stream))
+    return _m.sparse_attn_batched(shape, n_seq, q, k_cache, v_cache, idx, k_blk, v_blk, out, lse_out, stream)
 
 
 def mage_page_summary(shape: mage_shape, p: int, k_cache, summary, stream=None) -> int:
     """Per-page (max, min) key rows; see include/mage.h."""
-    return lib().mage_page_summary(ctypes.byref(shape), int(p), _ptr(k_cache), _ptr(summary), _stream(stream))
+    return _m.page_summary(shape, p, k_cache, summary, stream)
 
 
 def mage_quest_workspace_bytes(shape: mage_shape, p: int) -> int:
@@ -212,13 +218,12 @@ def mage_quest_workspace_bytes(shape: mage_shape, p: int) -> int:
 
 def mage_quest_select(shape: mage_shape, p: int, q, summary, idx_out, est_out, workspace, stream=None) -> int:
     """Estimated per-block KV subset from page summaries; see include/mage.h."""
-    return lib().mage_quest_select(ctypes.byref(shape), int(p), _ptr(q), _ptr(summary), _ptr(idx_out), _ptr(est_out),
-                                   _ptr(workspace), _wsize(workspace), _stream(stream))
+    return _m.quest_select(shape, p, q, summary, idx_out, est_out, workspace, stream)
 
 
 def mage_set_overlap(a, b, n_rows: int, k: int, a_rows: int, out, stream=None) -> int:
     """out[i] = |A_(i mod a_rows) & B_i| / k (Eq. 1, Eq. 3); see include/mage.h."""
-    return lib().mage_set_overlap(_ptr(a), _ptr(b), int(n_rows), int(k), int(a_rows), _ptr(out), _stream(stream))
+    return _m.set_overlap(a, b, n_rows, k, a_rows, out, stream)
 
 
 def mage_static_scratch_bytes() -> int:
@@ -227,8 +232,7 @@ def mage_static_scratch_bytes() -> int:
 
 def mage_select_static(shape: mage_shape, q1, k_cache, idx_out, alpha_out, stream=None) -> int:
     """mage_select on the library's static scratch array (no workspace, no allocation); see include/mage.h."""
-    return lib().mage_select_static(ctypes.byref(shape), _ptr(q1), _ptr(k_cache), _ptr(idx_out), _ptr(alpha_out),
-                                    _stream(stream))
+    return _m.select_static(shape, q1, k_cache, idx_out, alpha_out, stream)
 
 
 def mage_diag_empty(stream=None) -> int:
