@@ -90,6 +90,7 @@ KernelArgs base_args(const mage_shape &s, const SplitPlan &p)
     a.G = s.Hq / s.Hkv;
     a.R = p.R;
     a.rpad = p.rpad;
+    a.rw = p.rw;
     a.L = s.L;
     a.kps = p.kps;
     a.n_split = p.n_split;
@@ -255,7 +256,7 @@ int select_impl(const mage_shape *shape, float scale_log2, int key_weight, const
 
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     const bool bf = shape->dtype == MAGE_BF16;
-    a.gmax = bf ? reinterpret_cast<float *>(w + lay.gmax) : nullptr;   // the MFMA column sums also leave group maxima for the top-k filter
+    a.gmax = reinterpret_cast<float *>(w + lay.gmax);   // the column sums also leave group maxima for the top-k filter
     hipError_t e = bf ? bf16_stats(a, shape->d, p.row_groups, stream) : f32_stats(a, shape->d, p.row_groups, stream);
     if (e != hipSuccess) return MAGE_ERR_HIP;
     e = launch_lse(a, lse2, stream);
@@ -397,19 +398,10 @@ int mage_step1(const mage_shape *shape, const void *q1, const void *k_cache, con
     int rc = check_shape(shape, true);
     if (rc != MAGE_OK) return rc;
     if (!idx_out) return MAGE_ERR_NULL;
-    if (shape->dtype != MAGE_BF16) {
-        // fp32: the two calls back to back (no shared pass in the vector path); both are validated
-        // before the first one launches anything
-        rc = select_check(shape, q1, k_cache, idx_out, alpha_out, nullptr, workspace, workspace_bytes);
-        if (rc != MAGE_OK) return rc;
-        rc = run_attention(shape, plan_dense(*shape), false, q1, k_cache, v_cache, nullptr, k_blk, v_blk, out, lse_out,
-                           workspace, workspace_bytes, hip_stream);
-        if (rc != MAGE_OK) return rc;
-        return mage_select(shape, q1, k_cache, idx_out, alpha_out, workspace, workspace_bytes, hip_stream);
-    }
     const SplitPlan pa = plan_dense(*shape);
     const SplitPlan ps = plan_colsum(*shape);
-    if (ps.rpad > 256) return MAGE_ERR_UNSUPPORTED;
+    const bool bf = shape->dtype == MAGE_BF16;
+    if (bf && ps.rpad > 256) return MAGE_ERR_UNSUPPORTED;
     if (!aligned16(alpha_out)) return MAGE_ERR_ALIGN;
     const Step1Layout lay = step1_layout(*shape, pa);
     if (!workspace || workspace_bytes < lay.bytes) return MAGE_ERR_WORKSPACE;
@@ -439,7 +431,7 @@ int mage_step1(const mage_shape *shape, const void *q1, const void *k_cache, con
     a.lse2 = lse2;
     a.alpha = alpha_out ? alpha_out : reinterpret_cast<float *>(w + lay.alpha);
     a.gmax = reinterpret_cast<float *>(w + lay.gmax);
-    if (bf16_colsum(a, shape->d, ps.waves, stream) != hipSuccess) return MAGE_ERR_HIP;
+    if ((bf ? bf16_colsum(a, shape->d, ps.waves, stream) : f32_colsum(a, shape->d, stream)) != hipSuccess) return MAGE_ERR_HIP;
     if (launch_topk(a.alpha, a.gmax, shape->Hkv, shape->L, shape->k, idx_out,
                     rescore_args(*shape, a, stat_m, stat_l, pa.n_split, pa.rpad, a.scale_log2, 1), stream) != hipSuccess)
         return MAGE_ERR_HIP;

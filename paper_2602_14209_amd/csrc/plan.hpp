@@ -14,12 +14,10 @@
 namespace mage {
 
 constexpr int kBf16Tile = 64;   // keys per LDS tile, MFMA path
-constexpr int kF32Tile = 32;    // keys per LDS tile, fp32 vector path
-constexpr int kF32Rows = 64;    // query rows per workgroup, fp32 vector path
-constexpr int kTargetWorkgroups = 512;   // fp32 vector path: 2 per CU on 256 CUs
+constexpr int kF32Workgroups = 256;      // fp32 path, attention and statistics: one 8-wavefront workgroup per CU (registers)
+constexpr int kF32ColsumWorkgroups = 512;   // fp32 path, column sums: two 4-wavefront workgroups per CU
 constexpr int kBf16Workgroups = 256;     // MFMA path: one 8-wavefront workgroup per CU (its tile ring fills the LDS)
 constexpr int kStatsWorkgroups = 512;    // MFMA selection passes (row statistics, column sums): two per CU
-constexpr int kSelectWorkgroups = 2048;  // fp32 selection passes: 8 per CU
 
 struct SplitPlan {
     int R;            // query rows sharing one KV head: G*B
@@ -27,7 +25,8 @@ struct SplitPlan {
     int row_groups;   // workgroups along the row axis
     int rpad;         // row_groups * rows_per_wg
     int waves;        // wavefronts per workgroup of the column-sum pass (one per 32 rows; MFMA path)
-    int tile;         // keys per tile
+    int tile;         // keys per tile (fp32: keys a workgroup covers per round, 16 per key slice)
+    int rw;           // fp32: 16-row tiles per workgroup; its 8 wavefronts are rw row tiles x 8/rw key slices
     int kps;          // cache keys per split (multiple of tile)
     int n_split;      // splits along the key axis, including a block-only split if any
     int n_cyc;        // splits that own cache keys (the first n_cyc)
@@ -45,9 +44,11 @@ inline void plan_rows(const mage_shape &s, SplitPlan &p)
         p.waves = p.R > 128 ? 8 : 4;
         p.tile = kBf16Tile;
     } else {
+        // as many row tiles as there are, up to four: they read the same keys; the other wavefronts split the keys
         p.waves = 4;
-        p.rows_per_wg = kF32Rows;
-        p.tile = kF32Tile;
+        p.rw = p.R > 32 ? 4 : p.R > 16 ? 2 : 1;
+        p.rows_per_wg = 16 * p.rw;
+        p.tile = 16 * (8 / p.rw);
     }
     p.row_groups = ceil_div(p.R, p.rows_per_wg);
     p.rpad = p.row_groups * p.rows_per_wg;
@@ -60,12 +61,12 @@ inline SplitPlan plan_dense(const mage_shape &s, int target_workgroups = 0, bool
 {
     SplitPlan p{};
     plan_rows(s, p);
-    if (target_workgroups == 0) target_workgroups = s.dtype == MAGE_BF16 ? kBf16Workgroups : kTargetWorkgroups;
+    if (target_workgroups == 0) target_workgroups = s.dtype == MAGE_BF16 ? kBf16Workgroups : kF32Workgroups;
     const int64_t tiles = (s.L + p.tile - 1) / p.tile;
     const int64_t per_split = (int64_t)s.Hkv * (rows_in_one_workgroup ? 1 : p.row_groups);   // workgroups per key split
     const int64_t target = target_workgroups / per_split > 0 ? target_workgroups / per_split : 1;
     int64_t tps = (tiles + target - 1) / target;     // tiles per split
-    const int64_t min_tps = s.dtype == MAGE_BF16 ? 4 : 8;
+    const int64_t min_tps = 4;
     if (tps < min_tps) tps = min_tps;
     p.n_split = (int)((tiles + tps - 1) / tps);
     p.kps = (int)(tps * p.tile);
@@ -74,10 +75,10 @@ inline SplitPlan plan_dense(const mage_shape &s, int target_workgroups = 0, bool
     return p;
 }
 
-// Selection, first pass (row statistics).  The fp32 vector path uses one plan for both passes.
+// Selection, first pass (row statistics).
 inline SplitPlan plan_stats(const mage_shape &s)
 {
-    return plan_dense(s, s.dtype == MAGE_BF16 ? kStatsWorkgroups : kSelectWorkgroups);
+    return plan_dense(s, s.dtype == MAGE_BF16 ? kStatsWorkgroups : kF32Workgroups);
 }
 
 // Selection, second pass (column sums).  The MFMA kernel parks the sums of up to kColsumTiles tiles
@@ -90,30 +91,39 @@ constexpr int kGroupKeys = 16;           // keys per group maximum handed from t
 constexpr int kColsumWorkgroups4 = 768, kColsumWorkgroups8 = 512;
 inline SplitPlan plan_colsum(const mage_shape &s)
 {
-    if (s.dtype != MAGE_BF16) return plan_dense(s, kSelectWorkgroups);
+    if (s.dtype != MAGE_BF16) {
+        // a workgroup's four wavefronts take 32 keys each per round
+        SplitPlan p{};
+        plan_rows(s, p);
+        p.tile = 128;
+        const int64_t tiles = (s.L + p.tile - 1) / p.tile;
+        const int64_t target = kF32ColsumWorkgroups / s.Hkv > 0 ? kF32ColsumWorkgroups / s.Hkv : 1;
+        const int64_t tps = (tiles + target - 1) / target;
+        p.n_split = (int)((tiles + tps - 1) / tps);
+        p.kps = (int)(tps * p.tile);
+        p.blk_split = p.n_split - 1;
+        p.n_cyc = p.n_split;
+        return p;
+    }
     const int R = (s.Hq / s.Hkv) * s.B;
     return plan_dense(s, R > 128 ? kColsumWorkgroups8 : kColsumWorkgroups4, true);
 }
 
-// Sparse step: k gathered cache keys, in-block keys in a split of their own when k is large
-// enough for the gather splits to be full tiles.
+// Sparse step of the fp32 path: k gathered cache keys and the block's own.  Few keys stay in one split (one launch, the
+// key slices of a workgroup are merged on chip); beyond four rounds per workgroup the keys are split to fill the chip.
 inline SplitPlan plan_sparse(const mage_shape &s)
 {
     SplitPlan p{};
     plan_rows(s, p);
-    const int64_t tiles = ((int64_t)s.k + p.tile - 1) / p.tile;
-    const int64_t max_splits = 8;
-    const int64_t tps = (tiles + max_splits - 1) / max_splits;
-    const int n_cache = (int)((tiles + tps - 1) / tps);
+    const int64_t tiles = ((int64_t)s.k + s.B + p.tile - 1) / p.tile;
+    const int64_t per_split = (int64_t)s.Hkv * p.row_groups;
+    const int64_t target = kF32Workgroups / per_split > 0 ? kF32Workgroups / per_split : 1;
+    int64_t tps = (tiles + target - 1) / target;
+    if (tps < 4) tps = 4;
+    p.n_split = (int)((tiles + tps - 1) / tps);
     p.kps = (int)(tps * p.tile);
-    p.n_cyc = n_cache;
-    if (s.k >= p.tile) {
-        p.n_split = n_cache + 1;
-        p.blk_split = n_cache;
-    } else {
-        p.n_split = n_cache;
-        p.blk_split = n_cache - 1;
-    }
+    p.n_cyc = p.n_split;
+    p.blk_split = p.n_split - 1;
     return p;
 }
 
@@ -175,6 +185,7 @@ struct KernelArgs {
     int head_rows;           // column-sum pass: 0, or B = one grid row per QUERY head, summing that head's B rows only (Eq. 2 per head)
     float *gmax;             // column-sum pass, optional: [Hkv][ceil(L / kGroupKeys)] maxima of alpha over groups of consecutive keys
     int B, Hq, Hkv, G, R, rpad;
+    int rw;                  // fp32 path: row tiles per workgroup (SplitPlan::rw)
     long long L;             // rows in the cache
     long long nc;            // cache keys attended: L (dense) or k (gather)
     int kps, n_split, blk_split, n_blk;
