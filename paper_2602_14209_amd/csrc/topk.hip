@@ -3,22 +3,27 @@
 // emitted in ascending order.  alpha >= 0, so the order of the fp32 bit patterns as unsigned
 // integers is the order of the values.
 //
-// One workgroup of 1024 threads per KV head.  Two routes, chosen per head at run time:
-//   filter route (k small against L, the method's regime): the k-th largest of the maxima of
-//     disjoint groups of elements is a lower bound of the k-th largest element, so only the few
-//     elements at or above it can belong to the set; a radix select over those candidates in LDS
-//     finds the k-th value and the ties to keep, and a bitmap walk emits the positions in order.
-//     The whole route is one chain of short dependent phases on a single workgroup, so its time is
-//     the sum of their latencies: every radix step has its own pre-zeroed histogram and two
-//     barriers, prefix sums inside a wavefront use lane-shift moves, and wavefront-uniform values
-//     travel through scalar registers rather than the LDS crossbar.
-//     The group maxima either come with the row (the column-sum pass leaves one per kGroupKeys
-//     consecutive keys; only the groups at or above the bound are then read at all) or are
-//     taken here over 8192 strided groups in a first sweep of the row.
-//   radix route (any k, any tie structure; also the overflow exit of the filter route): three
-//     MSB-first radix-select steps over the whole row find the k-th value and the number of
-//     ties to keep, then an ordered sweep emits the set.
-// Near-ties at rank k (filter route): alpha is an fp32 result whose relative error (a few 1e-6 from the
+// One workgroup of 1024 threads per KV head.  The work is one chain of short dependent phases on a single
+// workgroup, so its time is the number of phases (a barrier each, 16 wavefronts on 4 SIMDs: every instruction of a
+// phase costs 16 issue cycles) plus the round trips to memory.  Hence ONE histogram instead of a radix select: alpha is a
+// probability, so its useful range is known beforehand and a bin is a fixed interval of the fp32 bit pattern
+// (value_bin: 64 octaves below 1.0, 64 bins per octave).  Everything above the bin that holds rank k is in, and only
+// the few elements of that bin and its two neighbours (1.6 % of a value each, typically 10 .. 100 elements) are ranked
+// exactly, all pairs at once.  Two routes:
+//   direct route: the row is binned element by element, then classified.  For rows that one sweep of registers
+//     holds (L <= 16384), and for large k, where a filter would let most of the row through.
+//   filter route (long rows, k <= L / 64): the k-th largest of the maxima of disjoint groups of elements is a lower bound
+//     of the k-th largest element.  The column-sum pass leaves one maximum per kGroupKeys consecutive keys; they are
+//     binned first and only the groups at or above the bound (about k of them) are read at all.
+// Membership is kept as a bitmap in LDS; walking it gives the positions in ascending order.
+// Measured (profiler) at k = 512: Hkv = 4, L = 8192: 19.7 us with the radix select that stood here (a filter in front of it
+// at every length, two digits for the bound and three for the k-th value), 6.2 us now; Hkv = 8, L = 131072: 18.4 us
+// before, 12.3 us now.  The row is read by a straight line of code that is fetched once, at about 13 cycles per
+// instruction, so what is not executed in the usual case (ragged ends, second sweeps, near-ties) sits behind branches.
+//   radix route (the exit for everything else: more ties around rank k than TK_LIST, more groups at
+//     or above the bound than TK_HITS, a k-th value below 2^-64, k > 2048 in a row longer than TK_BITMAP): three MSB-first radix-select steps over the whole row find the k-th value and the
+//     number of ties to keep, then an ordered sweep emits the set.
+// Near-ties at rank k: alpha is an fp32 result whose relative error (a few 1e-6 from the
 // fp32 dot products, exponentials and sums) is of the order of typical gaps between neighbouring values
 // at rank k, so the fp32 ranking can differ from the ranking of the exactly computed averages.  The
 // candidates within `eps` (relative) of the k-th value -- usually none, a handful at most -- are therefore
@@ -35,12 +40,14 @@ namespace mage {
 
 constexpr int TK_THREADS = 1024;
 constexpr int TK_WAVES = TK_THREADS / 64;
-constexpr int TK_BINS = 4096;                        // widest digit: 12 bits
-constexpr int TK_EPT = 16;                           // consecutive elements per thread in the ordered sweep
-constexpr int TK_SLOTS = 8;                          // group maxima per thread = loads in flight per thread
-constexpr int TK_GROUPS = TK_THREADS * TK_SLOTS;     // 8192
-constexpr int TK_CAND = 4096;                        // candidate capacity of the filter route
+constexpr int TK_BINS = 4096;
+constexpr int TK_EPT = 16;                           // elements per thread in a sweep of the row
+constexpr int TK_SWEEP = TK_THREADS * TK_EPT;        // elements one sweep covers
+constexpr int TK_HITS = 4096;                        // filter route: groups at or above the bound, at most
+constexpr int TK_NX = 4;                             // filter route: 16-byte pieces of those groups that a thread keeps in registers
 constexpr int TK_FILTER_MAX_K = 2048;
+constexpr int TK_LIST = 512;                         // elements around rank k that are ranked all pairs
+constexpr int TK_BITMAP = 262144;                    // positions whose membership bits LDS holds
 constexpr int TK_NEAR_MAX = 32;                      // candidates re-scored at most; more of them (massive ties) keep the fp32 ranking
 
 // Inclusive prefix sum over the 64 lanes of a wavefront with data-parallel-primitive moves
@@ -82,72 +89,39 @@ __device__ __forceinline__ uint32_t block_scan_incl(uint32_t v, uint32_t *tmp, u
     return x + lane_value(wi - w, wave);
 }
 
-// Radix step over elements held in LDS or global memory, for a histogram that is already zero
-// and used once: histogram the BITS-wide digit at `shift` of every element whose higher bits
-// equal `prefix` (bin = number of larger digits, so bins run from the top digit downwards),
-// then find the digit in which the `want`-th largest element falls.  Two barriers: after the
-// histogram, and after every wavefront has published the running sums of its threads' bins;
-// from those every wavefront works out the answer itself.  On return prefix has the digit
-// appended, want is the rank inside the digit's bucket and bucket its size.
-// Requires: at least `want` elements match the prefix.
-template <int BITS>
-__device__ __forceinline__ void radix_count(uint32_t x, bool in, int shift, uint32_t prefix, uint32_t *hist)
-{
-    constexpr int NB = 1 << BITS;
-    const uint32_t hi_mask = (shift + BITS >= 32) ? 0u : (0xffffffffu << (shift + BITS));
-    if (in && (x & hi_mask) == prefix) atomicAdd(&hist[NB - 1 - ((x >> shift) & (NB - 1))], 1u);
-}
+// Histogram bin of a value, larger values first: 64 bins per octave from 1.0 (bin 0) down to 2^-64.  What lies outside
+// (smaller values, the zeros behind the end of a row) has a bin number, taken as unsigned, beyond TK_BIN_LAST.
+// bin_floor: the smallest bit pattern in a bin -- value_bin(x) <= b exactly if x >= bin_floor(b).
+constexpr int TK_BIN_SHIFT = 17, TK_BIN_ONE = 0x3f800000 >> TK_BIN_SHIFT;
+constexpr uint32_t TK_BIN_LAST = TK_BINS - 2;
+__device__ __forceinline__ uint32_t value_bin(uint32_t x) { return (uint32_t)TK_BIN_ONE - (x >> TK_BIN_SHIFT); }
+__device__ __forceinline__ uint32_t bin_floor(int b) { return (uint32_t)(TK_BIN_ONE - b) << TK_BIN_SHIFT; }
 
-// UNR: independent loads in flight per thread (8 for rows in global memory; 1 for the few
-// candidates in LDS, where the instructions of the unused slots would cost more than the latency)
-template <int BITS, int UNR = 8>
-__device__ __forceinline__ void radix_hist_mem(const uint32_t *u, long long n, int shift, uint32_t prefix, uint32_t *hist)
+// Four consecutive elements of a row; rows start at any multiple of four bytes (the hardware loads 16 bytes from there in
+// one go).
+struct __attribute__((packed, aligned(4))) Piece { uint32_t v[4]; };
+
+// piece at element j (zeros past the end)
+__device__ __forceinline__ void load_piece_tail(const uint32_t *row, long long j, long long len, uint32_t (&x)[4])
 {
-    for (long long j0 = tid_x(); j0 < n; j0 += (long long)TK_THREADS * UNR) {
-        uint32_t x[UNR];
 #pragma unroll
-        for (int i = 0; i < UNR; ++i) {
-            const long long j = j0 + (long long)i * TK_THREADS;
-            x[i] = j < n ? u[j] : 0xffffffffu;
-        }
-#pragma unroll
-        for (int i = 0; i < UNR; ++i) radix_count<BITS>(x[i], j0 + (long long)i * TK_THREADS < n, shift, prefix, hist);
+    for (int c = 0; c < 4; ++c) {
+        const uint32_t v = row[j + c < len ? j + c : len - 1];
+        x[c] = j + c < len ? v : 0u;
     }
 }
 
-// the same over TK_SLOTS elements per thread that already sit in registers
-// `live` slots only: the slots past the end of a short row hold zeros, and thousands of them would all
-// be added, one after the other, to the single bin of the value zero; padding(...) accounts for them with
-// one addition.
-template <int BITS>
-__device__ __forceinline__ void radix_hist_regs(const uint32_t (&x)[TK_SLOTS], int live, int shift, uint32_t prefix, uint32_t *hist)
+// The bin in which the `want`-th largest element falls, the number of elements in the bins before it and its own
+// count.  Two barriers: after the histogram, and after every wavefront has published the running sums of its threads'
+// bins; from those every wavefront works out the answer itself.  Fewer than `want` elements in all: the last bin.
+__device__ __forceinline__ void pick_bin(const uint32_t *hist, uint32_t want, uint32_t *lscan, uint32_t *wtot, int &bin, uint32_t &before)
 {
-#pragma unroll
-    for (int i = 0; i < TK_SLOTS; ++i) radix_count<BITS>(x[i], i < live, shift, prefix, hist);
-}
-
-// n_pad elements of value zero, counted by one thread (they match a prefix of zero only)
-template <int BITS>
-__device__ __forceinline__ void radix_hist_padding(uint32_t n_pad, uint32_t prefix, uint32_t *hist)
-{
-    if (tid_x() == 0 && n_pad != 0 && prefix == 0) atomicAdd(&hist[(1 << BITS) - 1], n_pad);
-}
-
-template <int BITS>
-__device__ __forceinline__ void radix_pick(int shift, uint32_t &prefix, uint32_t &want, uint32_t &bucket,
-                                           const uint32_t *hist, uint32_t *lscan, uint32_t *wtot)
-{
-    constexpr int NB = 1 << BITS;
-    constexpr int PER = NB > TK_THREADS ? NB / TK_THREADS : 1;       // bins per thread
+    constexpr int PER = TK_BINS / TK_THREADS;
+    static_assert(PER == 4, "a thread reads its bins as one 16-byte load");
     const int lane = tid_x() & 63, wave = tid_x() >> 6;
     __syncthreads();
-    uint32_t mine = 0;
-#pragma unroll
-    for (int i = 0; i < PER; ++i) {
-        const int b = tid_x() * PER + i;
-        mine += b < NB ? hist[b] : 0u;
-    }
-    const uint32_t incl = wave_scan_incl(mine);
+    const uint4 c = *reinterpret_cast<const uint4 *>(hist + tid_x() * PER);
+    const uint32_t incl = wave_scan_incl(c.x + c.y + c.z + c.w);
     lscan[tid_x()] = incl;
     if (lane == 63) wtot[wave] = incl;
     __syncthreads();
@@ -155,38 +129,20 @@ __device__ __forceinline__ void radix_pick(int shift, uint32_t &prefix, uint32_t
     const uint32_t w = lane < TK_WAVES ? wtot[lane] : 0u;
     const uint32_t wi = wave_scan_incl(w);
     const unsigned long long wmask = __ballot(lane < TK_WAVES && wi >= want);
-    const int wsel = wmask ? __ffsll((long long)wmask) - 1 : TK_WAVES - 1;      // (never empty when the requirement holds)
+    const int wsel = wmask ? __ffsll((long long)wmask) - 1 : TK_WAVES - 1;
     const uint32_t wbase = lane_value(wi - w, wsel);                       // elements in the wavefronts before it
     const uint32_t v = lscan[wsel * 64 + lane];
     const unsigned long long lmask = __ballot(wbase + v >= want);
     const int lsel = lmask ? __ffsll((long long)lmask) - 1 : 63;
     const int tsel = wsel * 64 + lsel;
     uint32_t run = wbase + (lsel > 0 ? lane_value(v, lsel > 0 ? lsel - 1 : 0) : 0u);   // elements in the bins before that thread's
-    uint32_t digit_bin = (uint32_t)(tsel * PER), cnt = 0;
-#pragma unroll
-    for (int i = 0; i < PER; ++i) {
-        const int b = tsel * PER + i;
-        const uint32_t c = b < NB ? hist[b] : 0u;
-        if (cnt == 0) {
-            if (run < want && want <= run + c) {
-                digit_bin = (uint32_t)b;
-                cnt = c;
-            } else {
-                run += c;
-            }
-        }
-    }
-    prefix |= (uint32_t)(NB - 1 - digit_bin) << shift;
-    want -= run;
-    bucket = cnt;
-}
-
-template <int BITS>
-__device__ __forceinline__ void radix_step_once(const uint32_t *u, uint32_t n, int shift, uint32_t &prefix, uint32_t &want,
-                                                uint32_t &bucket, uint32_t *hist, uint32_t *lscan, uint32_t *wtot)
-{
-    for (uint32_t j = tid_x(); j < n; j += TK_THREADS) radix_count<BITS>(u[j], true, shift, prefix, hist);
-    radix_pick<BITS>(shift, prefix, want, bucket, hist, lscan, wtot);
+    const uint4 d = *reinterpret_cast<const uint4 *>(hist + tsel * PER);
+    int i = 0;
+    if (run + d.x < want) { run += d.x; i = 1;
+        if (run + d.y < want) { run += d.y; i = 2;
+            if (run + d.z < want) { run += d.z; i = 3; } } }
+    bin = tsel * PER + i;
+    before = run;
 }
 
 // One radix step over n elements of u (global or LDS): histogram the `bits`-wide digit at
@@ -247,63 +203,18 @@ __device__ __forceinline__ void radix_step(const uint32_t *u, long long n, int s
     __syncthreads();
 }
 
-// ascending bitonic sort of a[0..P) in LDS, P a power of two; every thread of the workgroup calls.
-// Thread t owns compare-exchange pairs t, t+1024, ...; for distances j <= 32 the 64 pairs of a
-// wavefront touch only that wavefront's own 128 elements, so those stages need no workgroup
-// barrier (LDS operations of one wavefront execute in order).
-template <class T>
-__device__ __forceinline__ void bitonic_sort(T *a, int P)
-{
-    bool need_barrier = true;
-    for (int k2 = 2; k2 <= P; k2 <<= 1)
-        for (int j = k2 >> 1; j > 0; j >>= 1) {
-            if (j >= 64 || need_barrier) __syncthreads();
-            else __builtin_amdgcn_wave_barrier();
-            need_barrier = j >= 64;          // the stage after a cross-wavefront stage must see its writes
-            for (int i = tid_x(); i < P / 2; i += TK_THREADS) {
-                const int lo = ((i & ~(j - 1)) << 1) | (i & (j - 1)), hi = lo | j;
-                const bool up = (lo & k2) == 0;
-                const T x = a[lo], y = a[hi];
-                if ((x > y) == up) {
-                    a[lo] = y;
-                    a[hi] = x;
-                }
-            }
-        }
-    __syncthreads();
-}
-
-// elements j..j+3 of row u (zero past the end); one 16-byte load when the row allows it
-__device__ __forceinline__ uint4 load4(const uint32_t *u, long long j, long long L, bool vec_ok)
-{
-    if (vec_ok) return j < L ? *reinterpret_cast<const uint4 *>(u + j) : make_uint4(0, 0, 0, 0);
-    uint4 r;
-    r.x = j < L ? u[j] : 0u;
-    r.y = j + 1 < L ? u[j + 1] : 0u;
-    r.z = j + 2 < L ? u[j + 2] : 0u;
-    r.w = j + 3 < L ? u[j + 3] : 0u;
-    return r;
-}
-
-__device__ __forceinline__ int pow2_at_least(int n)
-{
-    int p = 2;
-    while (p < n) p <<= 1;
-    return p;
-}
-
 __device__ __forceinline__ double load_elem(const void *p, long long i, int esz)
 {
     if (esz == 2) return (double)__uint_as_float((uint32_t)static_cast<const unsigned short *>(p)[i] << 16);
     return (double)static_cast<const float *>(p)[i];
 }
 
-// alpha[h, j] in fp64 from the inputs (Eq. 5) for the n listed candidates j = cidx[slot[c]]:
+// alpha[h, j] in fp64 from the inputs (Eq. 5) for n of the listed elements, j = list[slot[c]].y:
 //   1/(G*B) * sum over the R rows of exp2(q_r.k_j * scale - M_r) / L_r,
 // with (M_r, L_r) the row's softmax statistics merged in fp64 over the key splits.  Four threads per
 // row (a quarter of the channels and of the splits each), 256 rows per pass.  Every thread of the
 // workgroup calls; out[c] receives the results rounded to fp32 (valid after the final barrier).
-__device__ void rescore_candidates(const RescoreArgs &rs, int h, const uint32_t *cidx, const uint32_t *slot, int n, float *out,
+__device__ __forceinline__ void rescore_candidates(const RescoreArgs &rs, int h, const uint2 *list, const uint32_t *slot, int n, float *out,
                                    float *rowM, double *rowL, double *acc, double *red)
 {
     constexpr int ROWS = TK_THREADS / 4;
@@ -336,7 +247,7 @@ __device__ void rescore_candidates(const RescoreArgs &rs, int h, const uint32_t 
         const int gl = live ? r / rs.B : 0, qi = live ? r - gl * rs.B : 0;
         const long long qo = ((long long)qi * rs.Hq + (long long)h * rs.G + gl) * rs.d + part * cpt;
         for (int c = 0; c < n; ++c) {
-            const long long j = (long long)cidx[slot[c]];
+            const long long j = (long long)list[slot[c]].y;
             const long long ko = (j * rs.Hkv + h) * rs.d + part * cpt;
             double p = 0.0;
             if (live)
@@ -361,27 +272,50 @@ __device__ void rescore_candidates(const RescoreArgs &rs, int h, const uint32_t 
     __syncthreads();
 }
 
+// Bits [0, n) of the bitmap in ascending order (bits from n to the next multiple of 16 are zero): emit(rank, position)
+// for every set bit, rank counted from `first`; returns the number of set bits.  The caller has put a barrier between
+// the last change of the bitmap and this.
+template <class Emit>
+__device__ __forceinline__ uint32_t walk_bitmap(const uint32_t *bits, int n, uint32_t first, uint32_t *tmp, Emit emit)
+{
+    const uint16_t *half = reinterpret_cast<const uint16_t *>(bits);
+    const int hw = (n + 15) >> 4, per = (hw + TK_THREADS - 1) / TK_THREADS;     // 16 positions at a time, `per` of them per thread
+    uint32_t mine = 0;
+    for (int i = 0; i < per; ++i) {
+        const int w = tid_x() * per + i;
+        if (w < hw) mine += __popc((uint32_t)half[w]);
+    }
+    uint32_t total;
+    uint32_t rank = first + block_scan_incl(mine, tmp, total) - mine;
+    if (mine != 0) {
+        for (int i = 0; i < per; ++i) {
+            const int w = tid_x() * per + i;
+            uint32_t b = w < hw ? half[w] : 0u;
+            while (b) {
+                emit(rank, w * 16 + __ffs(b) - 1);
+                ++rank;
+                b &= b - 1;
+            }
+        }
+    }
+    return total;
+}
+
 __global__ __launch_bounds__(TK_THREADS) void topk_kernel(const float *alpha, const float *group_max, long long L, int k, int32_t *idx_out,
                                                           const RescoreArgs rs)
 {
-    // one histogram per radix step of the filter route, zeroed together at the start; the radix
-    // route reuses the first TK_BINS entries
-    constexpr int H_G1 = 0, H_G2 = H_G1 + 4096, H_C1 = H_G2 + 256, H_C2 = H_C1 + 4096, H_C3 = H_C2 + 1024, H_ALL = H_C3 + 1024;
-    __shared__ uint32_t hists[H_ALL];
-    static_assert(H_ALL >= TK_BINS, "the radix route histograms 12-bit digits in the same array");
-    uint32_t *hist = hists;
+    __shared__ __attribute__((aligned(16))) uint32_t hist[TK_BINS + 64], hist2[TK_BINS];      // (the last 64 of hist: elements outside the bins)
+    __shared__ __attribute__((aligned(16))) uint32_t bits[TK_BITMAP / 32];                    // membership by position
     __shared__ uint32_t lscan[TK_THREADS];
     __shared__ uint32_t tmp[TK_WAVES + 1];
     __shared__ uint32_t tmp2[TK_WAVES + 1];
-    __shared__ uint32_t bcast[3];                        // chosen digit, rank inside its bucket, bucket size
-    __shared__ uint32_t n_cand;
-    __shared__ uint32_t gmax[TK_GROUPS];                 // group maxima, later the index sort buffer
-    __shared__ uint32_t cval[TK_CAND];                   // candidate values (fp32 bit patterns)
-    __shared__ uint32_t cidx[TK_CAND];                   // and their positions
-    __shared__ uint32_t glist[TK_CAND];                  // groups at or above the bound (handed-in maxima only)
-    __shared__ uint32_t n_hit;
-    __shared__ uint32_t n_near, n_near_in;
-    __shared__ uint32_t near_slot[TK_NEAR_MAX];          // candidates within eps of the k-th value
+    __shared__ uint32_t bcast[3];                        // radix route: chosen digit, rank inside its bucket, bucket size
+    __shared__ uint32_t glist[TK_HITS];                  // filter route: groups at or above the bound
+    __shared__ uint32_t winners[TK_FILTER_MAX_K];        // positions in the set, for rows longer than the bitmap
+    __shared__ uint2 list[TK_LIST];                      // (value, position) around rank k
+    __shared__ uint32_t ltake[TK_LIST];
+    __shared__ uint32_t n_hit, n_cand, n_win, n_list, n_near, n_near_in, thr_bits, next_bits;
+    __shared__ uint32_t near_slot[TK_NEAR_MAX];          // list entries within eps of the k-th value
     __shared__ float near_val[TK_NEAR_MAX];              // their fp64 score, rounded to fp32
     __shared__ double red64[TK_WAVES], near_acc[TK_NEAR_MAX], rowL[TK_THREADS / 4];
     __shared__ float rowM[TK_THREADS / 4];
@@ -389,271 +323,288 @@ __global__ __launch_bounds__(TK_THREADS) void topk_kernel(const float *alpha, co
     const int h = wg_x();
     const uint32_t *u = reinterpret_cast<const uint32_t *>(alpha) + (long long)h * L;
     int32_t *out = idx_out + (long long)h * k;
+    const int ng = (int)((L + kGroupKeys - 1) / kGroupKeys);          // group maxima of the row
+    // a row of one sweep is binned directly; so is a longer one whose groups would mostly pass the filter
+    const bool filter = L > TK_SWEEP && k <= ng / 4 && k <= TK_FILTER_MAX_K;
 
-    if (k <= TK_FILTER_MAX_K) {
-        const bool vec_ok = (L & 3) == 0 && (reinterpret_cast<uintptr_t>(u) & 15) == 0;
-        const int lane = tid_x() & 63;
-        const long long ng = (L + kGroupKeys - 1) / kGroupKeys;       // handed-in group maxima
-        // the maxima buffer serves the last phase only (position bitmap / index sort buffer)
-        const bool bitmap = L <= (long long)TK_GROUPS * 32;
-        uint32_t *bits = gmax;
-        int32_t *sidx = reinterpret_cast<int32_t *>(gmax);
-        const int words = (int)((L + 31) >> 5);
-        const int P2 = pow2_at_least(k);
-        // This thread's group maxima, group = slot * 1024 + thread: handed in (if they fit: up to
-        // TK_GROUPS of them, the rest reads as zero) or taken here; ranked and compared from
-        // registers.  More handed-in maxima than that are ranked from global memory.
-        uint32_t gv[TK_SLOTS];
-        const uint32_t *gg = group_max ? reinterpret_cast<const uint32_t *>(group_max) + (long long)h * ng : nullptr;
-        const bool in_regs = group_max == nullptr || ng <= TK_GROUPS;
+    if (filter || L <= TK_BITMAP) {
+        const int t = tid_x(), lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+        const uint32_t *row = filter ? reinterpret_cast<const uint32_t *>(group_max) + (long long)h * ng : u;
+        const int len = filter ? ng : (int)L;
+        // This thread's elements of a sweep: `per` consecutive ones (8 if that covers the row: then every wavefront has
+        // work), in 16-byte pieces.
+        const int per = len <= TK_SWEEP / 2 ? TK_EPT / 2 : TK_EPT;
+        uint32_t x[TK_EPT / 4][4];
+        auto sweep = [&](int j0) {
+            const int j = j0 + t * per;
+            if (j0 + (wave + 1) * 64 * per <= len) {      // uniform: nothing of this wavefront is past the end
 #pragma unroll
-        for (int s = 0; s < TK_SLOTS; ++s) gv[s] = 0u;
-        if (group_max != nullptr) {
-            if (in_regs) {
+                for (int i = 0; i < TK_EPT / 4; ++i)
+                    if (4 * i < per) {                    // uniform
+                        const Piece p = *reinterpret_cast<const Piece *>(row + j + 4 * i);
 #pragma unroll
-                for (int s = 0; s < TK_SLOTS; ++s) {
-                    const int g = s * TK_THREADS + tid_x();
-                    if (g < ng) gv[s] = gg[g];
-                }
-            }
-        } else {
-            // ---- sweep 1: strided group maxima; each thread takes 4 consecutive elements per slot
-            // (one 16-byte load when the row is aligned)
-            for (long long base0 = 0; base0 < L; base0 += 4ll * TK_GROUPS) {
-                uint4 x[TK_SLOTS];
+                        for (int c = 0; c < 4; ++c) x[i][c] = p.v[c];
+                    }
+            } else {
 #pragma unroll
-                for (int s = 0; s < TK_SLOTS; ++s) x[s] = load4(u, base0 + 4ll * (s * TK_THREADS + tid_x()), L, vec_ok);
-#pragma unroll
-                for (int s = 0; s < TK_SLOTS; ++s) {
-                    const uint32_t a = x[s].x > x[s].y ? x[s].x : x[s].y, b = x[s].z > x[s].w ? x[s].z : x[s].w;
-                    const uint32_t c = a > b ? a : b;
-                    gv[s] = c > gv[s] ? c : gv[s];
-                }
-            }
-        }
-        // while the loads travel: every histogram and the buffer of the last phase start at zero
-        for (int i = tid_x(); i < H_ALL; i += TK_THREADS) hists[i] = 0u;
-        if (bitmap) for (int i = tid_x(); i < words; i += TK_THREADS) bits[i] = 0u;
-        else for (int i = tid_x(); i < P2; i += TK_THREADS) sidx[i] = 0x7fffffff;
-        if (tid_x() == 0) {
-            n_cand = 0;
-            n_hit = 0;
-            n_near = 0;
-            n_near_in = 0;
-        }
-        __syncthreads();
-        // a lower bound of the k-th largest group maximum (its top 20 bits), hence of the k-th
-        // largest element: at least k elements are >= floor_bits
-        uint32_t floor_bits = 0, rank = (uint32_t)k, bucket;
-        // slots of this thread that hold a group (group = slot * 1024 + thread); the zeros behind the end of a
-        // short row take part in the ranking as one bulk count
-        const long long mine = ng > tid_x() ? (ng - tid_x() + TK_THREADS - 1) / TK_THREADS : 0;
-        const int live = (group_max != nullptr && in_regs) ? (int)(mine < TK_SLOTS ? mine : TK_SLOTS) : TK_SLOTS;
-        const uint32_t n_pad = (group_max != nullptr && in_regs) ? (uint32_t)(TK_GROUPS - ng) : 0u;
-        if (in_regs) {
-            radix_hist_regs<12>(gv, live, 20, floor_bits, hists + H_G1);
-            radix_hist_padding<12>(n_pad, floor_bits, hists + H_G1);
-        } else {
-            radix_hist_mem<12>(gg, ng, 20, floor_bits, hists + H_G1);
-        }
-        radix_pick<12>(20, floor_bits, rank, bucket, hists + H_G1, lscan, tmp);
-        if (in_regs) {
-            radix_hist_regs<8>(gv, live, 12, floor_bits, hists + H_G2);
-            radix_hist_padding<8>(n_pad, floor_bits, hists + H_G2);
-        } else {
-            radix_hist_mem<8>(gg, ng, 12, floor_bits, hists + H_G2);
-        }
-        radix_pick<8>(12, floor_bits, rank, bucket, hists + H_G2, lscan, tmp2);
-
-        // appends this thread's `cnt` keepers among x[0..NX) (positions j[i] .. j[i]+3) to the candidates
-        auto keep = [&](const uint4 *x, const long long *j, int nx, uint32_t cnt) {
-            const uint32_t incl = wave_scan_incl(cnt);
-            const uint32_t wave_total = lane_value(incl, 63);
-            if (wave_total == 0) return;                   // uniform per wavefront
-            uint32_t base = 0;
-            if (lane == 0) base = atomicAdd(&n_cand, wave_total);
-            uint32_t pos = lane_value(base, 0) + incl - cnt;
-            if (cnt) {
-                for (int s = 0; s < nx; ++s) {
-                    const uint32_t xs[4] = {x[s].x, x[s].y, x[s].z, x[s].w};
-#pragma unroll
-                    for (int c = 0; c < 4; ++c)
-                        if (j[s] >= 0 && j[s] + c < L && xs[c] >= floor_bits) {
-                            if (pos < TK_CAND) {
-                                cval[pos] = xs[c];
-                                cidx[pos] = (uint32_t)(j[s] + c);
-                            }
-                            ++pos;
-                        }
-                }
+                for (int i = 0; i < TK_EPT / 4; ++i)
+                    if (4 * i < per) load_piece_tail(row, j + 4 * i, len, x[i]);
             }
         };
-        bool overflow = false;
-        if (group_max != nullptr) {
-            // ---- the groups at or above the bound, then only their elements ----
-            for (long long g0 = 0; g0 < ng; g0 += (long long)TK_THREADS * TK_SLOTS) {     // uniform trip count (one if in_regs)
-                if (!in_regs) {
+        sweep(0);
+        // while the loads travel
+        reinterpret_cast<uint4 *>(hist)[t] = make_uint4(0, 0, 0, 0);
+        if (filter) {
+            reinterpret_cast<uint4 *>(hist2)[t] = make_uint4(0, 0, 0, 0);
+            const int zero = (int)((L < TK_BITMAP ? L : TK_BITMAP) + 127) / 128;
+            for (int i = t; i < zero; i += TK_THREADS) reinterpret_cast<uint4 *>(bits)[i] = make_uint4(0, 0, 0, 0);
+        }
+        if (t == 0) {
+            n_hit = 0;
+            n_cand = 0;
+            n_win = 0;
+            n_list = 0;
+            next_bits = 0;
+        }
+        __syncthreads();
+
+        for (int j0 = 0; j0 < len; j0 += TK_SWEEP) {
+            if (j0 > 0) sweep(j0);
+            if (j0 + wave * 64 * per < len) {             // uniform
 #pragma unroll
-                    for (int s = 0; s < TK_SLOTS; ++s) {
-                        const long long g = g0 + (long long)s * TK_THREADS + tid_x();
-                        gv[s] = g < ng ? gg[g] : 0u;
-                    }
-                }
-                uint32_t cnt = 0;
+                for (int i = 0; i < TK_EPT / 4; ++i)
+                    if (4 * i < per)
 #pragma unroll
-                for (int s = 0; s < TK_SLOTS; ++s) {
-                    const long long g = g0 + (long long)s * TK_THREADS + tid_x();
-                    cnt += (g < ng && gv[s] >= floor_bits);
-                }
-                const uint32_t incl = wave_scan_incl(cnt);
-                const uint32_t wave_total = lane_value(incl, 63);
-                if (wave_total == 0) continue;
-                uint32_t base = 0;
-                if (lane == 0) base = atomicAdd(&n_hit, wave_total);
-                uint32_t pos = lane_value(base, 0) + incl - cnt;
-#pragma unroll
-                for (int s = 0; s < TK_SLOTS; ++s) {
-                    const long long g = g0 + (long long)s * TK_THREADS + tid_x();
-                    if (g < ng && gv[s] >= floor_bits) {
-                        if (pos < TK_CAND) glist[pos] = (uint32_t)g;
-                        ++pos;
-                    }
-                }
+                        for (int c = 0; c < 4; ++c) {
+                            const uint32_t b = value_bin(x[i][c]);
+                            atomicAdd(&hist[b <= TK_BIN_LAST ? b : (uint32_t)(TK_BINS + lane)], 1u);
+                        }
             }
-            __syncthreads();
-            const uint32_t nh = n_hit;
-            overflow = nh > TK_CAND;
-            if (!overflow) {
-                constexpr int QPG = kGroupKeys / 4;            // 16-byte pieces per group
-                constexpr int NX = 4;                           // pieces in flight per thread
-                const uint32_t items = nh * QPG;
-                for (uint32_t i0 = 0; i0 < items; i0 += TK_THREADS * NX) {                // uniform trip count
-                    uint4 x[NX];
-                    long long j[NX];
+        }
+        int bin;
+        uint32_t before;
+        pick_bin(hist, (uint32_t)k, lscan, tmp, bin, before);
+        bool give_up = bin > (int)TK_BIN_LAST - 1;        // uniform: leave for the radix route
+
+        // one bit per element of x that is at least `floor`
+        auto at_least = [&](uint32_t floor) {
+            uint32_t m = 0;
 #pragma unroll
-                    for (int s = 0; s < NX; ++s) {
-                        const uint32_t i = i0 + s * TK_THREADS + tid_x();
-                        j[s] = i < items ? (long long)glist[i / QPG] * kGroupKeys + 4 * (i % QPG) : -1;
-                        x[s] = j[s] >= 0 ? load4(u, j[s], L, vec_ok) : make_uint4(0, 0, 0, 0);
-                    }
-                    uint32_t cnt = 0;
+            for (int i = 0; i < TK_EPT / 4; ++i)
+                if (4 * i < per)
 #pragma unroll
-                    for (int s = 0; s < NX; ++s)
-                        if (j[s] >= 0)
-                            cnt += (j[s] < L && x[s].x >= floor_bits) + (j[s] + 1 < L && x[s].y >= floor_bits) +
-                                   (j[s] + 2 < L && x[s].z >= floor_bits) + (j[s] + 3 < L && x[s].w >= floor_bits);
-                    keep(x, j, NX, cnt);
+                    for (int c = 0; c < 4; ++c) m |= (x[i][c] >= floor ? 1u : 0u) << (4 * i + c);
+            return m;
+        };
+        // elements around rank k: bit e of `m` = position j + e
+        auto append = [&](uint32_t m, int j) {
+            if (m == 0) return;
+            uint32_t p = atomicAdd(&n_list, (uint32_t)__popc(m));
+            while (m) {
+                const int e = __ffs(m) - 1;
+                if (p < TK_LIST) list[p] = make_uint2(u[j + e], (uint32_t)(j + e));
+                ++p;
+                m &= m - 1;
+            }
+        };
+        uint32_t want;                                    // how many of the listed elements belong to the set
+        if (!filter) {
+            want = (uint32_t)k - (before - (bin > 0 ? hist[bin - 1] : 0u));
+            // in: the bins before the neighbourhood of `bin`; listed: `bin` and its two neighbours
+            for (int j0 = 0; j0 < len && !give_up; j0 += TK_SWEEP) {
+                if (len > TK_SWEEP) sweep(j0);
+                if (j0 + wave * 64 * per < len) {
+                    const uint32_t in = at_least(bin_floor(bin - 2));
+                    append(at_least(bin_floor(bin + 1)) & ~in, j0 + t * per);
+                    if (per == 8) reinterpret_cast<uint8_t *>(bits)[t] = (uint8_t)in;
+                    else reinterpret_cast<uint16_t *>(bits)[(j0 >> 4) + t] = (uint16_t)in;
                 }
             }
         } else {
-            // ---- sweep 2: keep the elements at or above the bound ----
-            for (long long base0 = 0; base0 < L; base0 += 4ll * TK_GROUPS) {      // uniform trip count
-                uint4 x[TK_SLOTS];
-                long long j[TK_SLOTS];
-#pragma unroll
-                for (int s = 0; s < TK_SLOTS; ++s) {
-                    j[s] = base0 + 4ll * (s * TK_THREADS + tid_x());
-                    x[s] = load4(u, j[s], L, vec_ok);
+            // ---- groups at or above the bound: one bin below the k-th largest maximum, so that the neighbours of rank
+            // k's bin are complete
+            const uint32_t floor = bin_floor(bin + 1);
+            for (int j0 = 0; j0 < len && !give_up; j0 += TK_SWEEP) {
+                if (len > TK_SWEEP) sweep(j0);
+                uint32_t m = j0 + wave * 64 * per < len ? at_least(floor) : 0u;
+                const uint32_t cnt = __popc(m), incl = wave_scan_incl(cnt), all = lane_value(incl, 63);
+                if (all == 0) continue;                   // uniform per wavefront
+                uint32_t base = 0;
+                if (lane == 0) base = atomicAdd(&n_hit, all);
+                uint32_t p = lane_value(base, 0) + incl - cnt;
+                while (m) {
+                    if (p < TK_HITS) glist[p] = (uint32_t)(j0 + t * per + __ffs(m) - 1);
+                    ++p;
+                    m &= m - 1;
                 }
+            }
+            __syncthreads();
+            // ---- their elements, 16 bytes per thread: kept in registers while TK_NX pieces per thread cover them
+            const uint32_t nh = n_hit;
+            give_up = give_up || nh > TK_HITS;
+            constexpr int QPG = kGroupKeys / 4;           // pieces per group
+            const int items = give_up ? 0 : (int)nh * QPG;
+            int jp[TK_NX];
+            auto fetch = [&](int i0) {
+#pragma unroll
+                for (int i = 0; i < TK_NX; ++i)
+                    if (i0 + i * TK_THREADS < items) {    // uniform
+                        const int it = i0 + i * TK_THREADS + t;
+                        jp[i] = (int)glist[it < items ? it / QPG : 0] * kGroupKeys + 4 * (it % QPG);
+                        if (it >= items) {
+                            x[i][0] = x[i][1] = x[i][2] = x[i][3] = 0u;
+                        } else if (jp[i] + 4 <= L) {
+                            const Piece pc = *reinterpret_cast<const Piece *>(u + jp[i]);
+#pragma unroll
+                            for (int c = 0; c < 4; ++c) x[i][c] = pc.v[c];
+                        } else {
+                            load_piece_tail(u, jp[i], L, x[i]);
+                        }
+                    }
+            };
+            for (int i0 = 0; i0 < items; i0 += TK_NX * TK_THREADS) {
+                fetch(i0);
                 uint32_t cnt = 0;
 #pragma unroll
-                for (int s = 0; s < TK_SLOTS; ++s)
-                    cnt += (j[s] < L && x[s].x >= floor_bits) + (j[s] + 1 < L && x[s].y >= floor_bits) +
-                           (j[s] + 2 < L && x[s].z >= floor_bits) + (j[s] + 3 < L && x[s].w >= floor_bits);
-                keep(x, j, TK_SLOTS, cnt);
+                for (int i = 0; i < TK_NX; ++i)
+                    if (i0 + i * TK_THREADS < items)
+#pragma unroll
+                        for (int c = 0; c < 4; ++c)
+                            if (x[i][c] >= floor) {
+                                atomicAdd(&hist2[value_bin(x[i][c])], 1u);
+                                ++cnt;
+                            }
+                cnt = lane_value(wave_scan_incl(cnt), 63);
+                if (lane == 0 && cnt) atomicAdd(&n_cand, cnt);
+            }
+            __syncthreads();
+            // ---- the bin of rank k, counted from below: usually within an octave of the bound (groups hold few
+            // elements of the set each), which one read of the histogram per wavefront covers
+            const uint32_t nc = n_cand;
+            const uint32_t c = bin + 1 - lane >= 0 ? hist2[bin + 1 - lane] : 0u;
+            const uint32_t low = wave_scan_incl(c);                       // elements in this lane's bin and below
+            const unsigned long long mask = __ballot(low > nc - (uint32_t)k);
+            if (mask) {                                   // uniform
+                const int d = __ffsll((long long)mask) - 1;
+                bin = bin + 1 - d;
+                before = nc - lane_value(low, d);
+            } else {
+                pick_bin(hist2, (uint32_t)k, lscan, tmp2, bin, before);
+            }
+            want = (uint32_t)k - (before - (bin > 0 ? hist2[bin - 1] : 0u));
+            const uint32_t in_floor = bin_floor(bin - 2), list_floor = bin_floor(bin + 1);
+            for (int i0 = 0; i0 < items; i0 += TK_NX * TK_THREADS) {
+                if (items > TK_NX * TK_THREADS) fetch(i0);
+#pragma unroll
+                for (int i = 0; i < TK_NX; ++i)
+                    if (i0 + i * TK_THREADS < items) {
+                        uint32_t in = 0, near = 0;
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            in |= (x[i][e] >= in_floor ? 1u : 0u) << e;
+                            near |= (x[i][e] >= list_floor ? 1u : 0u) << e;
+                        }
+                        append(near & ~in, jp[i]);
+                        if (in == 0) continue;
+                        if (L <= TK_BITMAP) {
+                            atomicOr(&bits[jp[i] >> 5], in << (jp[i] & 31));
+                        } else {
+                            for (; in; in &= in - 1) {
+                                const uint32_t p = atomicAdd(&n_win, 1u);
+                                if (p < TK_FILTER_MAX_K) winners[p] = (uint32_t)(jp[i] + __ffs(in) - 1);
+                            }
+                        }
+                    }
             }
         }
         __syncthreads();
-        const uint32_t nc = n_cand;
-        if (!overflow && nc <= TK_CAND) {
-            // exact k-th value among the candidates (radix select in LDS) and the number of
-            // candidates equal to it that belong to the set (the ones with the smallest positions)
-            uint32_t thr = 0, want = (uint32_t)k, n_equal;
-            radix_step_once<12>(cval, nc, 20, thr, want, n_equal, hists + H_C1, lscan, tmp);
-            radix_step_once<10>(cval, nc, 10, thr, want, n_equal, hists + H_C2, lscan, tmp2);
-            radix_step_once<10>(cval, nc, 0, thr, want, n_equal, hists + H_C3, lscan, tmp);
-            // n_cand now counts the winners (index-sort route); every thread read nc before the
-            // barriers of the radix steps
-            if (!bitmap) {
-                if (tid_x() == 0) n_cand = 0;
-                __syncthreads();
+        const uint32_t nl = n_list;
+        if (!give_up && nl <= TK_LIST) {
+            // ---- rank of every listed element (value, then smaller position), 16 threads per element
+            for (uint32_t i0 = 0; i0 < nl; i0 += TK_THREADS / 16) {
+                const uint32_t i = i0 + (t >> 4);
+                const uint2 me = list[i < nl ? i : 0];
+                uint32_t rank = 0;
+                for (uint32_t o = t & 15; o < nl; o += 16) {
+                    const uint2 other = list[o];
+                    rank += other.x > me.x || (other.x == me.x && other.y < me.y);
+                }
+                constexpr int ROW_ROR = 0x120;            // rotation inside a row of 16 lanes
+                rank += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)rank, ROW_ROR + 1, 0xf, 0xf, true);
+                rank += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)rank, ROW_ROR + 2, 0xf, 0xf, true);
+                rank += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)rank, ROW_ROR + 4, 0xf, 0xf, true);
+                rank += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)rank, ROW_ROR + 8, 0xf, 0xf, true);
+                if ((t & 15) == 0 && i < nl) {
+                    ltake[i] = rank < want;
+                    if (rank + 1 == want) thr_bits = me.x;
+                    if (rank == want) next_bits = me.x;
+                    if (rank < want && L <= TK_BITMAP) atomicOr(&bits[me.y >> 5], 1u << (me.y & 31));
+                }
             }
-            // who is in by the fp32 ranking (ctake); the candidates within eps of the k-th value are listed
-            uint32_t *ctake = glist;                         // (the group list has served its purpose)
-            const float thr_f = __uint_as_float(thr);
+            __syncthreads();
+            // ---- near-ties: the first element left out is within eps of the k-th value
+            const float thr_f = __uint_as_float(thr_bits);
             const uint32_t near_lo = __float_as_uint(thr_f * (1.f - rs.eps)), near_hi = __float_as_uint(thr_f * (1.f + rs.eps));
-            const bool rescoring = rs.q != nullptr;
-            for (uint32_t i = tid_x(); i < nc; i += TK_THREADS) {
-                const uint32_t v = cval[i], j = cidx[i];
-                bool take = v > thr;
-                if (v == thr) {
-                    take = true;
-                    if (n_equal != want) {                   // ties cut: keep the `want` smallest positions
-                        uint32_t below = 0;
-                        for (uint32_t t = 0; t < nc; ++t) below += (cval[t] == thr && cidx[t] < j);
-                        take = below < want;
-                    }
-                }
-                ctake[i] = take;
-                if (rescoring && v >= near_lo && v <= near_hi) {
-                    const uint32_t slot = atomicAdd(&n_near, 1u);
-                    if (slot < TK_NEAR_MAX) near_slot[slot] = i;
-                    if (take) atomicAdd(&n_near_in, 1u);
-                }
-            }
-            __syncthreads();
-            const uint32_t nn = n_near, nin = n_near_in;
-            if (rescoring && nn >= 2 && nn <= TK_NEAR_MAX && nin >= 1 && nin < nn) {   // uniform; rare
-                rescore_candidates(rs, h, cidx, near_slot, (int)nn, near_val, rowM, rowL, near_acc, red64);
-                if (tid_x() < nn) {                      // rank among the near candidates: value, then smaller position
-                    const uint32_t me = near_slot[tid_x()];
-                    const float v = near_val[tid_x()];
-                    uint32_t rank = 0;
-                    for (uint32_t c = 0; c < nn; ++c) {
-                        const uint32_t o = near_slot[c];
-                        rank += (near_val[c] > v) || (near_val[c] == v && cidx[o] < cidx[me]);
-                    }
-                    ctake[me] = rank < nin;
+            if (next_bits >= near_lo) {                   // uniform; rare
+                if (t == 0) {
+                    n_near = 0;
+                    n_near_in = 0;
                 }
                 __syncthreads();
-            }
-            for (uint32_t i = tid_x(); i < nc; i += TK_THREADS) {
-                if (ctake[i]) {
-                    const uint32_t j = cidx[i];
-                    if (bitmap) atomicOr(&bits[j >> 5], 1u << (j & 31));
-                    else sidx[atomicAdd(&n_cand, 1u)] = (int32_t)j;
+                if (t < (int)nl && list[t].x >= near_lo && list[t].x <= near_hi) {
+                    const uint32_t slot = atomicAdd(&n_near, 1u);
+                    if (slot < TK_NEAR_MAX) near_slot[slot] = t;
+                    if (ltake[t]) atomicAdd(&n_near_in, 1u);
                 }
-            }
-            __syncthreads();
-            if (bitmap) {
-                // ascending order by walking the bitmap of the L positions
-                const int wpt = (words + TK_THREADS - 1) / TK_THREADS;      // consecutive words per thread (<= 8)
-                uint32_t mine = 0;
-                for (int i = 0; i < wpt; ++i) {
-                    const int wi = tid_x() * wpt + i;
-                    if (wi < words) mine += __popc(bits[wi]);
-                }
-                uint32_t total;
-                uint32_t pos = block_scan_incl(mine, tmp, total) - mine;
-                for (int i = 0; i < wpt; ++i) {
-                    const int wi = tid_x() * wpt + i;
-                    if (wi < words) {
-                        uint32_t b = bits[wi];
-                        while (b) {
-                            const int bit = __ffs(b) - 1;
-                            if (pos < (uint32_t)k) out[pos] = (int32_t)(wi * 32 + bit);
-                            ++pos;
-                            b &= b - 1;
+                __syncthreads();
+                const uint32_t nn = n_near, nin = n_near_in;
+                if (nn <= TK_NEAR_MAX) {                 // more of them (massive ties) keep the fp32 ranking
+                    rescore_candidates(rs, h, list, near_slot, (int)nn, near_val, rowM, rowL, near_acc, red64);
+                    if (t < (int)nn) {                   // rank among the near elements: value, then smaller position
+                        const uint32_t me = near_slot[t], j = list[me].y;
+                        const float v = near_val[t];
+                        uint32_t rank = 0;
+                        for (uint32_t c = 0; c < nn; ++c) rank += (near_val[c] > v) || (near_val[c] == v && list[near_slot[c]].y < j);
+                        ltake[me] = rank < nin;
+                        if (L <= TK_BITMAP) {
+                            if (rank < nin) atomicOr(&bits[j >> 5], 1u << (j & 31));
+                            else atomicAnd(&bits[j >> 5], ~(1u << (j & 31)));
                         }
                     }
                 }
-            } else {
-                bitonic_sort(sidx, P2);
-                for (int i = tid_x(); i < k; i += TK_THREADS) out[i] = sidx[i];
+                __syncthreads();
+            }
+            if (L <= TK_BITMAP) {
+                walk_bitmap(bits, (int)L, 0u, tmp2, [&](uint32_t rank, int j) {
+                    if (rank < (uint32_t)k) out[rank] = j;
+                });
+                return;
+            }
+            // rows longer than the bitmap: one stretch of positions after the other
+            if (t < (int)nl && ltake[t]) {
+                const uint32_t p = atomicAdd(&n_win, 1u);
+                if (p < TK_FILTER_MAX_K) winners[p] = list[t].y;
+            }
+            uint32_t done = 0;
+            for (long long j0 = 0; j0 < L; j0 += TK_BITMAP) {
+                __syncthreads();
+                for (int i = t; i < k; i += TK_THREADS) {
+                    const long long j = (long long)winners[i] - j0;
+                    if (j >= 0 && j < TK_BITMAP) atomicOr(&bits[j >> 5], 1u << (j & 31));
+                }
+                __syncthreads();
+                done += walk_bitmap(bits, TK_BITMAP, done, tmp2, [&](uint32_t rank, int j) {
+                    if (rank < (uint32_t)k) out[rank] = (int32_t)(j0 + j);
+                });
+                __syncthreads();
+                for (int i = t; i < k; i += TK_THREADS) {                // leave the bitmap empty
+                    const long long j = (long long)winners[i] - j0;
+                    if (j >= 0 && j < TK_BITMAP) bits[j >> 5] = 0u;
+                }
             }
             return;
         }
-        __syncthreads();                                 // too many ties at the bound: radix route
+        __syncthreads();                                  // the radix route reuses the histogram
     }
 
     // ---- radix route: threshold = bit pattern of the k-th largest value; want = how many
@@ -666,7 +617,7 @@ __global__ __launch_bounds__(TK_THREADS) void topk_kernel(const float *alpha, co
 
     // ordered sweep: element j goes to slot (#greater before j) + min(#equal before j, want)
     uint32_t base_gt = 0, base_eq = 0;
-    for (long long c0 = 0; c0 < L; c0 += (long long)TK_THREADS * TK_EPT) {
+    for (long long c0 = 0; c0 < L; c0 += TK_SWEEP) {
         const long long j0 = c0 + (long long)tid_x() * TK_EPT;
         uint32_t x[TK_EPT];
         uint32_t ngt = 0, neq = 0;
@@ -698,7 +649,7 @@ __global__ __launch_bounds__(TK_THREADS) void topk_kernel(const float *alpha, co
     }
 }
 
-// group_max: nullptr, or [Hkv][ceil(L / kGroupKeys)] maxima of alpha over groups of kGroupKeys consecutive positions
+// group_max: [Hkv][ceil(L / kGroupKeys)] maxima of alpha over groups of kGroupKeys consecutive positions
 hipError_t launch_topk(const float *alpha, const float *group_max, int Hkv, long long L, int k, int32_t *idx_out, const RescoreArgs &rs,
                        hipStream_t stream)
 {
