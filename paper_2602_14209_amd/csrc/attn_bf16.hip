@@ -31,6 +31,7 @@
 #include "lds_asm.hpp"
 #include "ids.hpp"
 #include "plan.hpp"
+#include "row_stats.hpp"
 
 namespace mage {
 
@@ -742,8 +743,11 @@ void colsum_bf16_kernel(const KernelArgs a)
     constexpr int NBUF = 3;                                         // LDS tile buffers = prefetch distance + 1
     constexpr int LPT = G::LOADS / NW;                              // loads one wavefront issues per tile
     __shared__ __attribute__((aligned(1024))) unsigned char smem[NBUF * BUF_BYTES];
-    __shared__ float red[2][NW][kBf16Tile];
-    __shared__ float ring[kColsumTiles][kBf16Tile];
+    // red [2][NW][64], ring [kColsumTiles][64]; before the first tile: scratch of the statistics merge, 12 bytes per thread
+    constexpr int RED_BYTES = 2 * NW * kBf16Tile * 4, RING_BYTES = kColsumTiles * kBf16Tile * 4;
+    static_assert(RED_BYTES + RING_BYTES >= NW * 64 * 12, "the merge fits");
+    __shared__ __attribute__((aligned(16))) unsigned char aux[RED_BYTES + RING_BYTES];
+    __shared__ __attribute__((aligned(16))) float lse_lds[NW * 32];
     static_assert(kColsumTiles % NW == 0, "flush deals the ring slots to the wavefronts");
 
     // One grid row per KV head sums all G*B rows of the head (Eq. 5); with head_rows = B there is
@@ -786,21 +790,41 @@ void colsum_bf16_kernel(const KernelArgs a)
                                      [&](int r) -> long long { return base + (r < valid ? r : valid - 1); });
         }
     };
+    // requested first, because everything is waited for in order: the row statistics, the queries, the tiles
+    RowStats<NW * 64> stats;
+    if (a.lse2 == nullptr) stats.issue(a, h, row_lo, R);
+    bf16x8_t qf[KS];
+    load_q_frag<D>(a, static_cast<const u16 *>(a.q), h, row_lo + row0 + l32, qf);
 #pragma unroll
     for (int t = 0; t < NBUF - 1; ++t)
         if (t < ntiles) issue(t);
-
-    bf16x8_t qf[KS];
-    load_q_frag<D>(a, static_cast<const u16 *>(a.q), h, row_lo + row0 + l32, qf);
     FragAddr fa = frag_addr<D>(lane);
     const unsigned smem_addr = lds_addr(smem);
 
     // per-register row statistics: register v is query row row_lo + row0 + 8*(v/4) + 4*lg + v%4
     float lse2[16];
+    if (a.lse2 == nullptr) {
+        stats.finish(a, lds_addr(lse_lds), lds_addr(aux));
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        __syncthreads();
+        u32x4_t four[4];
+        const unsigned at = lds_addr(lse_lds) + (row0 + 4 * lg) * 4;
+        static_for<4>([&](auto I) { four[decltype(I)::value] = lds_read_b128<32 * decltype(I)::value>(at); });
+        static_for<4>([&](auto I) {
+            constexpr int i = decltype(I)::value;
+            lds_wait<3 - i>(four[i]);
 #pragma unroll
-    for (int v = 0; v < 16; ++v) {
-        const int r = row0 + 8 * (v >> 2) + 4 * lg + (v & 3);
-        lse2[v] = r < R ? a.lse2[(long long)h * a.rpad + row_lo + r] : INFINITY;   // exp2(-inf) = 0 for rows outside the sum
+            for (int e = 0; e < 4; ++e) lse2[4 * i + e] = __uint_as_float(four[i][e]);
+        });
+#pragma unroll
+        for (int v = 0; v < 16; ++v)
+            if (row0 + 8 * (v >> 2) + 4 * lg + (v & 3) >= R) lse2[v] = INFINITY;       // exp2(-inf) = 0 for rows outside the sum
+    } else {
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            const int r = row0 + 8 * (v >> 2) + 4 * lg + (v & 3);
+            lse2[v] = r < R ? a.lse2[(long long)h * a.rpad + row_lo + r] : INFINITY;
+        }
     }
 
     // The cross-wavefront sum of tile t is finished after the barrier of tile t+1 (the `red`
@@ -808,7 +832,7 @@ void colsum_bf16_kernel(const KernelArgs a)
     // leave together: a global store inside the loop would sit in the same counter as the tile
     // loads and hold up the wavefront that issued it at every barrier.  `red` and `ring` are read
     // and written with inline assembly for the same reason as the tiles.
-    const unsigned red_addr = lds_addr(red), ring_addr = lds_addr(ring);
+    const unsigned red_addr = lds_addr(aux), ring_addr = lds_addr(aux) + RED_BYTES;
     auto finish = [&](int t) {
         if (tid_x() < kBf16Tile) {
             const unsigned src = red_addr + ((t & 1) * NW * kBf16Tile + tid_x()) * 4;

@@ -24,6 +24,7 @@
 
 #include "ids.hpp"
 #include "plan.hpp"
+#include "row_stats.hpp"
 
 namespace mage {
 
@@ -269,7 +270,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void c
     const int l16 = lane & 15, lg = lane >> 4;
     const float *kc = static_cast<const float *>(a.kc) + (long long)h * D;
     const unsigned stride = (unsigned)a.Hkv * D;
-    const float *lse2 = a.lse2 + (long long)h * a.rpad;
+    __shared__ float lse_lds[kMergeRows];
+    __shared__ __attribute__((aligned(8))) unsigned char scratch[256 * 12];
+    const float *lse2 = a.lse2 + (long long)h * a.rpad;            // by row of the KV head
+    if (a.lse2 == nullptr) {
+        RowStats<256> stats;
+        stats.issue(a, h, row_lo, row_end - row_lo);
+        stats.finish(a, lds_addr(lse_lds), lds_addr(scratch));
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        __syncthreads();
+    }
     const long long n_groups = (a.L + kGroupKeys - 1) / kGroupKeys;
     const int units = (int)((a.L + 31) / 32);
 
@@ -292,7 +302,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void c
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
                 const int r = r0 + 4 * lg + v;
-                ls[v] = r < row_end ? lse2[r] : INFINITY;            // exp2(-inf) = 0 for rows outside the sum
+                const bool in = r < row_end;                         // exp2(-inf) = 0 for rows outside the sum
+                ls[v] = a.lse2 == nullptr ? (in ? lse_lds[r - row_lo] : INFINITY) : (in ? lse2[r] : INFINITY);
             }
             const f32v4_t s0 = f32_scores<D>(q, k[0]), s1 = f32_scores<D>(q, k[1]);      // query r0 + 4*lg + v, key l16
             if (r0 + 16 < row_end) load_q(r0 + 16);

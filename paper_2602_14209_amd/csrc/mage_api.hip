@@ -26,7 +26,7 @@ hipError_t launch_quest_query(const void *q, void *q2, long long rows, int d, hi
 hipError_t launch_expand_pages(const int32_t *pages, int32_t *idx, int Hkv, int k, int p, hipStream_t stream);
 hipError_t launch_overlap(const int32_t *a, const int32_t *b, int n_rows, int k, int a_rows, float *out, hipStream_t stream);
 hipError_t launch_topk(const float *alpha, const float *group_max, int Hkv, long long L, int k, int32_t *idx_out, const RescoreArgs &rs,
-                       hipStream_t stream);
+                       const KernelArgs *comb, int d, hipStream_t stream);
 }  // namespace mage
 
 using namespace mage;
@@ -128,11 +128,12 @@ int attention_check(const mage_shape *shape, const SplitPlan &p, bool gather,
     return MAGE_OK;
 }
 
+// `deferred`: the caller merges the split partials (if there are any) with these arguments in a launch of its own.
 int run_attention(const mage_shape *shape, const SplitPlan &p, bool gather,
                   const void *q, const void *k_cache, const void *v_cache, const int32_t *idx,
                   const void *k_blk, const void *v_blk, float *out, float *lse_out,
                   void *workspace, size_t workspace_bytes, void *hip_stream,
-                  float *stat_m = nullptr, float *stat_l = nullptr, float *lse2_out = nullptr)
+                  float *stat_m = nullptr, float *stat_l = nullptr, KernelArgs *deferred = nullptr)
 {
     const int rc = attention_check(shape, p, gather, q, k_cache, v_cache, idx, k_blk, v_blk, out, workspace, workspace_bytes);
     if (rc != MAGE_OK) return rc;
@@ -151,14 +152,15 @@ int run_attention(const mage_shape *shape, const SplitPlan &p, bool gather,
     a.lse_out = lse_out;
     a.stat_m = stat_m;
     a.stat_l = stat_l;
-    a.lse2_out = p.n_split > 1 ? lse2_out : nullptr;
     if (p.n_split > 1) carve_partials(*shape, p, workspace, a);
 
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     hipError_t e = shape->dtype == MAGE_BF16 ? bf16_attn(a, shape->d, p.row_groups, stream)
                                              : f32_attn(a, shape->d, p.row_groups, gather, stream);
     if (e != hipSuccess) return MAGE_ERR_HIP;
-    if (p.n_split > 1) {
+    if (deferred) {
+        *deferred = a;
+    } else if (p.n_split > 1) {
         e = launch_combine(a, shape->d, stream);
         if (e != hipSuccess) return MAGE_ERR_HIP;
     }
@@ -250,8 +252,8 @@ int select_impl(const mage_shape *shape, float scale_log2, int key_weight, const
     a.nc = shape->L;
     a.part_m = reinterpret_cast<float *>(w + lay.part_m);
     a.part_l = reinterpret_cast<float *>(w + lay.part_l);
+    a.stat_split = p.n_split;
     float *lse2 = reinterpret_cast<float *>(w + lay.lse2);
-    a.lse2 = lse2;
     a.alpha = alpha_out ? alpha_out : reinterpret_cast<float *>(w + lay.alpha);
 
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
@@ -259,8 +261,11 @@ int select_impl(const mage_shape *shape, float scale_log2, int key_weight, const
     a.gmax = reinterpret_cast<float *>(w + lay.gmax);   // the column sums also leave group maxima for the top-k filter
     hipError_t e = bf ? bf16_stats(a, shape->d, p.row_groups, stream) : f32_stats(a, shape->d, p.row_groups, stream);
     if (e != hipSuccess) return MAGE_ERR_HIP;
-    e = launch_lse(a, lse2, stream);
-    if (e != hipSuccess) return MAGE_ERR_HIP;
+    if (!colsum_merges_stats(p.R, p.n_split)) {
+        e = launch_lse(a, lse2, stream);
+        if (e != hipSuccess) return MAGE_ERR_HIP;
+        a.lse2 = lse2;
+    }
     KernelArgs c = a;                                // the column sums have their own split of the keys
     c.kps = pc.kps;
     c.n_split = pc.n_split;
@@ -269,7 +274,8 @@ int select_impl(const mage_shape *shape, float scale_log2, int key_weight, const
         e = bf ? bf16_colsum(c, shape->d, pc.waves, stream) : f32_colsum(c, shape->d, stream);
         if (e != hipSuccess) return MAGE_ERR_HIP;
         e = launch_topk(a.alpha, a.gmax, shape->Hkv, shape->L, shape->k, idx_out,
-                        rescore_args(*shape, a, a.part_m, a.part_l, p.n_split, p.rpad, scale_log2, key_weight), stream);
+                        rescore_args(*shape, a, a.part_m, a.part_l, p.n_split, p.rpad, scale_log2, key_weight),
+                        nullptr, shape->d, stream);
         if (e != hipSuccess) return MAGE_ERR_HIP;
     }
     if (pbar_out) {                                  // the same sums restricted to the B rows of one query head at a time
@@ -408,17 +414,12 @@ int mage_step1(const mage_shape *shape, const void *q1, const void *k_cache, con
     char *w = static_cast<char *>(workspace);
     float *stat_m = reinterpret_cast<float *>(w + lay.stat_m), *stat_l = reinterpret_cast<float *>(w + lay.stat_l);
     float *lse2 = reinterpret_cast<float *>(w + lay.lse2);
+    KernelArgs comb{};
     rc = run_attention(shape, pa, false, q1, k_cache, v_cache, nullptr, k_blk, v_blk, out, lse_out,
-                       w + lay.partials, lay.stat_m - lay.partials, hip_stream, stat_m, stat_l, lse2);
+                       w + lay.partials, lay.stat_m - lay.partials, hip_stream, stat_m, stat_l, &comb);
     if (rc != MAGE_OK) return rc;
 
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-    if (pa.n_split == 1) {                           // unsplit keys: no combine pass ran, merge the one statistics set here
-        KernelArgs r = base_args(*shape, pa);
-        r.part_m = stat_m;
-        r.part_l = stat_l;
-        if (launch_lse(r, lse2, stream) != hipSuccess) return MAGE_ERR_HIP;
-    }
     KernelArgs a = base_args(*shape, ps);            // column sums on selection's own, finer split
     a.q = q1;
     a.kc = k_cache;
@@ -428,12 +429,22 @@ int mage_step1(const mage_shape *shape, const void *q1, const void *k_cache, con
     a.n_blk = 0;
     a.blk_split = -1;
     a.nc = shape->L;
-    a.lse2 = lse2;
+    a.part_m = stat_m;
+    a.part_l = stat_l;
+    a.stat_split = pa.n_split;
     a.alpha = alpha_out ? alpha_out : reinterpret_cast<float *>(w + lay.alpha);
     a.gmax = reinterpret_cast<float *>(w + lay.gmax);
+    if (!colsum_merges_stats(pa.R, pa.n_split)) {
+        KernelArgs r = a;
+        r.n_split = pa.n_split;
+        if (launch_lse(r, lse2, stream) != hipSuccess) return MAGE_ERR_HIP;
+        a.lse2 = lse2;
+    }
     if ((bf ? bf16_colsum(a, shape->d, ps.waves, stream) : f32_colsum(a, shape->d, stream)) != hipSuccess) return MAGE_ERR_HIP;
+    // the split partials of the attention are merged beside the top-k, which leaves nearly the whole chip idle
     if (launch_topk(a.alpha, a.gmax, shape->Hkv, shape->L, shape->k, idx_out,
-                    rescore_args(*shape, a, stat_m, stat_l, pa.n_split, pa.rpad, a.scale_log2, 1), stream) != hipSuccess)
+                    rescore_args(*shape, a, stat_m, stat_l, pa.n_split, pa.rpad, a.scale_log2, 1),
+                    pa.n_split > 1 ? &comb : nullptr, shape->d, stream) != hipSuccess)
         return MAGE_ERR_HIP;
     return MAGE_OK;
 }

@@ -109,6 +109,11 @@ inline SplitPlan plan_colsum(const mage_shape &s)
     return plan_dense(s, R > 128 ? kColsumWorkgroups8 : kColsumWorkgroups4, true);
 }
 
+// Do the column sums merge the row statistics themselves (row_stats.hpp)?  Every one of their workgroups then reads the
+// statistics of all splits: 1 us of L2 time at 128 splits of 128 rows, still less than the launch it saves.
+constexpr int kMergeSplits = 128, kMergeRows = 256;
+inline bool colsum_merges_stats(int rows, int n_split) { return rows <= kMergeRows && n_split <= kMergeSplits; }
+
 // Sparse step of the fp32 path: k gathered cache keys and the block's own.  Few keys stay in one split (one launch, the
 // key slices of a workgroup are merged on chip); beyond four rounds per workgroup the keys are split to fill the chip.
 inline SplitPlan plan_sparse(const mage_shape &s)
@@ -179,8 +184,8 @@ struct KernelArgs {
     float *out, *lse_out;    // final outputs (used directly when n_split == 1)
     float *part_o, *part_m, *part_l;
     float *stat_m, *stat_l;  // exact attention, optional: prefix-only (cache keys) statistics per split, as part_m/part_l
-    const float *lse2;       // column-sum pass: per-row log2-domain log-sum-exp [Hkv][rpad]
-    float *lse2_out;         // combine, optional: the same, merged from stat_m / stat_l
+    const float *lse2;       // column-sum pass: per-row log2-domain log-sum-exp [Hkv][rpad]; nullptr: merged there from part_m / part_l
+    int stat_split;          // ... of this many splits
     float *alpha;            // column-sum pass: [Hkv][L] (or [Hq][L] with head_rows)
     int head_rows;           // column-sum pass: 0, or B = one grid row per QUERY head, summing that head's B rows only (Eq. 2 per head)
     float *gmax;             // column-sum pass, optional: [Hkv][ceil(L / kGroupKeys)] maxima of alpha over groups of consecutive keys

@@ -33,6 +33,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "combine.hpp"
 #include "ids.hpp"
 #include "plan.hpp"
 
@@ -301,9 +302,22 @@ __device__ __forceinline__ uint32_t walk_bitmap(const uint32_t *bits, int n, uin
     return total;
 }
 
+// DC: head dimension of attention partials that the workgroups from n_heads on merge (four query rows each), 0 = none.
+// In the fused step 1 that merge (5 to 8 us as a launch of its own) depends on nothing but the attention pass and runs
+// beside the top-k's few workgroups.
+template <int DC>
 __global__ __launch_bounds__(TK_THREADS) void topk_kernel(const float *alpha, const float *group_max, long long L, int k, int32_t *idx_out,
-                                                          const RescoreArgs rs)
+                                                          const RescoreArgs rs, int n_heads, const KernelArgs comb)
 {
+    if constexpr (DC > 0) {
+        __shared__ CombineLds<DC> comb_lds[TK_THREADS / 256];
+        if ((int)wg_x() >= n_heads) {                    // uniform
+            const int sub = tid_x() >> 8;
+            const int item = ((int)wg_x() - n_heads) * (TK_THREADS / 256) + sub, ch = item / comb.R;
+            combine_row<DC>(comb, item - ch * comb.R, ch, tid_x() & 255, ch < comb.Hkv, comb_lds[sub]);
+            return;
+        }
+    }
     __shared__ __attribute__((aligned(16))) uint32_t hist[TK_BINS + 64], hist2[TK_BINS];      // (the last 64 of hist: elements outside the bins)
     __shared__ __attribute__((aligned(16))) uint32_t bits[TK_BITMAP / 32];                    // membership by position
     __shared__ uint32_t lscan[TK_THREADS];
@@ -650,10 +664,21 @@ __global__ __launch_bounds__(TK_THREADS) void topk_kernel(const float *alpha, co
 }
 
 // group_max: [Hkv][ceil(L / kGroupKeys)] maxima of alpha over groups of kGroupKeys consecutive positions
+// comb: nullptr, or the arguments of an attention call (head dimension d) whose split partials are merged in the same launch
 hipError_t launch_topk(const float *alpha, const float *group_max, int Hkv, long long L, int k, int32_t *idx_out, const RescoreArgs &rs,
-                       hipStream_t stream)
+                       const KernelArgs *comb, int d, hipStream_t stream)
 {
-    hipLaunchKernelGGL(topk_kernel, dim3(Hkv), dim3(TK_THREADS), 0, stream, alpha, group_max, L, k, idx_out, rs);
+    dim3 grid(Hkv), block(TK_THREADS);
+    if (!comb) {
+        hipLaunchKernelGGL(topk_kernel<0>, grid, block, 0, stream, alpha, group_max, L, k, idx_out, rs, Hkv, KernelArgs{});
+        return hipGetLastError();
+    }
+    const long long rows = (long long)comb->R * Hkv, per = TK_THREADS / 256;
+    if ((rows + per - 1) / per + Hkv > 0x7fffffff) return hipErrorInvalidValue;
+    grid.x = Hkv + (unsigned)((rows + per - 1) / per);
+    if (d == 128) hipLaunchKernelGGL(topk_kernel<128>, grid, block, 0, stream, alpha, group_max, L, k, idx_out, rs, Hkv, *comb);
+    else if (d == 64) hipLaunchKernelGGL(topk_kernel<64>, grid, block, 0, stream, alpha, group_max, L, k, idx_out, rs, Hkv, *comb);
+    else return hipErrorInvalidValue;
     return hipGetLastError();
 }
 
