@@ -17,7 +17,6 @@ constexpr int kBf16Tile = 64;   // keys per LDS tile, MFMA path
 constexpr int kF32Workgroups = 256;      // fp32 path, attention and statistics: one 8-wavefront workgroup per CU (registers)
 constexpr int kF32ColsumWorkgroups = 512;   // fp32 path, column sums: two 4-wavefront workgroups per CU
 constexpr int kBf16Workgroups = 256;     // MFMA path: one 8-wavefront workgroup per CU (its tile ring fills the LDS)
-constexpr int kStatsWorkgroups = 512;    // MFMA selection passes (row statistics, column sums): two per CU
 
 struct SplitPlan {
     int R;            // query rows sharing one KV head: G*B
@@ -54,9 +53,11 @@ inline void plan_rows(const mage_shape &s, SplitPlan &p)
     p.rpad = p.row_groups * p.rows_per_wg;
 }
 
-// Dense pass over all L cache keys.  Exact attention pays a [rows x d] partial per split, so it
-// aims at two workgroups per CU; the two passes of selection leave only a (max, sum) pair per
-// row and split, so they cut the keys much finer (more workgroups in flight, even tail).
+// Dense pass over all L cache keys, cut into at most `target_workgroups`.  A CU that holds one workgroup more than the
+// others ends that much later, so the count stays at or below a multiple of 256: with tiles of 64 keys, 33 splits of 8 heads (264
+// workgroups of 2 tiles) measured 16.5 us where 22 splits (176 of 3 tiles) take 12.9.  Every workgroup pays a fixed 4 to
+// 5 us (cold code, first tile, merge), so up to 64 tiles go one per split (L = 1500, B = 8, 16 heads: 11.0 us against 13.2
+// with at least four); beyond that a split has at least two, because exact attention pays a [rows x d] partial per split.
 inline SplitPlan plan_dense(const mage_shape &s, int target_workgroups = 0, bool rows_in_one_workgroup = false)
 {
     SplitPlan p{};
@@ -66,7 +67,7 @@ inline SplitPlan plan_dense(const mage_shape &s, int target_workgroups = 0, bool
     const int64_t per_split = (int64_t)s.Hkv * (rows_in_one_workgroup ? 1 : p.row_groups);   // workgroups per key split
     const int64_t target = target_workgroups / per_split > 0 ? target_workgroups / per_split : 1;
     int64_t tps = (tiles + target - 1) / target;     // tiles per split
-    const int64_t min_tps = 4;
+    const int64_t min_tps = s.dtype == MAGE_BF16 ? (tiles <= 64 ? 1 : 2) : 4;
     if (tps < min_tps) tps = min_tps;
     p.n_split = (int)((tiles + tps - 1) / tps);
     p.kps = (int)(tps * p.tile);
@@ -75,10 +76,13 @@ inline SplitPlan plan_dense(const mage_shape &s, int target_workgroups = 0, bool
     return p;
 }
 
-// Selection, first pass (row statistics).
+// Selection, first pass (row statistics).  Two workgroups fit a CU.  With few query rows they are worth having (memory
+// latency: B*G = 32, L = 32768: 35.0 against 35.8 us for the selection); with more than 64 the vector ALU is busy with one, and
+// half as many splits are half as many statistics to merge (B*G = 224, L = 32768: 37.1 against 40.7 us).
 inline SplitPlan plan_stats(const mage_shape &s)
 {
-    return plan_dense(s, s.dtype == MAGE_BF16 ? kStatsWorkgroups : kF32Workgroups);
+    const int R = (s.Hq / s.Hkv) * s.B;
+    return plan_dense(s, s.dtype == MAGE_BF16 ? (R > 64 ? 1 : 2) * kBf16Workgroups : kF32Workgroups);
 }
 
 // Selection, second pass (column sums).  The MFMA kernel parks the sums of up to kColsumTiles tiles
@@ -86,9 +90,9 @@ inline SplitPlan plan_stats(const mage_shape &s)
 // workgroup pays a pipeline fill) and a power-of-two number of them.
 constexpr int kColsumTiles = 8;
 constexpr int kGroupKeys = 16;           // keys per group maximum handed from the column sums to the top-k filter
-// The MFMA kernel keeps all rows of a KV head in one workgroup (4 or 8 wavefronts); its registers
-// and LDS let three 4-wavefront or two 8-wavefront workgroups share a CU.
-constexpr int kColsumWorkgroups4 = 768, kColsumWorkgroups8 = 512;
+// The MFMA kernel keeps all rows of a KV head in one workgroup.  4 wavefronts: three workgroups fit a CU; at d = 64
+// three are the fastest, at d = 128 two (L = 32768: 40.1 against 41.8 us).  8 wavefronts: one per CU while its tiles fit the
+// ring of finished sums (L = 16411: 33.0 us for the selection against 35.2 with 260 workgroups), then two.
 inline SplitPlan plan_colsum(const mage_shape &s)
 {
     if (s.dtype != MAGE_BF16) {
@@ -106,7 +110,9 @@ inline SplitPlan plan_colsum(const mage_shape &s)
         return p;
     }
     const int R = (s.Hq / s.Hkv) * s.B;
-    return plan_dense(s, R > 128 ? kColsumWorkgroups8 : kColsumWorkgroups4, true);
+    if (R <= 128) return plan_dense(s, (s.d == 64 ? 3 : 2) * kBf16Workgroups, true);
+    const SplitPlan one = plan_dense(s, kBf16Workgroups, true);
+    return one.kps <= kColsumTiles * one.tile ? one : plan_dense(s, 2 * kBf16Workgroups, true);
 }
 
 // Do the column sums merge the row statistics themselves (row_stats.hpp)?  Every one of their workgroups then reads the
