@@ -32,21 +32,19 @@ struct RowStats {
     static constexpr int CHUNK = 16;                  // splits a thread has in flight
     float m[CHUNK], l[CHUNK];
     int rows32, parts, part, row;
-    const float *pm, *pl;
+    unsigned off, step, last;                         // element offsets from (head, split 0, row 0): this thread's next split, from one to the next, the last split
+    const float *pm, *pl;                             // uniform
     bool live;
 
-    // splits s0 + part, s0 + part + parts, ...; past the last split the last one again (weighted zero in finish)
-    __device__ __forceinline__ void request(const KernelArgs &a, int s0)
+    // the next CHUNK of the splits part, part + parts, ...; past the last split the last one again (weighted zero in finish)
+    __device__ __forceinline__ void request()
     {
-        int s = s0 + part;
-        const int last = a.stat_split - 1;
 #pragma unroll
         for (int i = 0; i < CHUNK; ++i) {
-            const unsigned off = (unsigned)(s < last ? s : last) * (unsigned)a.rpad;
-            m[i] = pm[off];
-            l[i] = pl[off];
-            if (s > last) l[i] = 0.f;
-            s += parts;
+            const unsigned at = off < last ? off : last;
+            m[i] = pm[at];
+            l[i] = pl[at];
+            off += step;
         }
     }
 
@@ -57,27 +55,35 @@ struct RowStats {
         part = (int)tid_x() / rows32;
         row = (int)tid_x() - part * rows32;
         live = part < parts && row < rows;
-        const long long base = (long long)h * a.stat_split * a.rpad + row_lo + (live ? row : 0);
+        const long long base = (long long)h * a.stat_split * a.rpad + row_lo;
         pm = a.part_m + base;
         pl = a.part_l + base;
-        request(a, 0);
+        const unsigned r = live ? row : 0;
+        off = (unsigned)part * (unsigned)a.rpad + r;
+        step = (unsigned)parts * (unsigned)a.rpad;
+        last = (unsigned)(a.stat_split - 1) * (unsigned)a.rpad + r;
+        request();
     }
 
     __device__ __forceinline__ void finish(const KernelArgs &a, unsigned dst, unsigned scratch)
     {
         float M = -3.0e38f;
         double sum = 0.0;
-        for (int s0 = 0;;) {                              // one round unless there are more than CHUNK splits per part
+        for (int s0 = CHUNK * parts;; s0 += CHUNK * parts) {      // one round unless there are more than CHUNK splits per part
             float top = M;
 #pragma unroll
             for (int i = 0; i < CHUNK; ++i) top = fmaxf(top, m[i]);
             sum *= (double)__builtin_amdgcn_exp2f(M - top);
             M = top;
+            unsigned at = off - CHUNK * step;
 #pragma unroll
-            for (int i = 0; i < CHUNK; ++i) sum += (double)(l[i] * __builtin_amdgcn_exp2f(m[i] - M));
-            s0 += CHUNK * parts;
+            for (int i = 0; i < CHUNK; ++i) {
+                const float w = l[i] * __builtin_amdgcn_exp2f(m[i] - M);
+                sum += (double)(at <= last ? w : 0.f);
+                at += step;
+            }
             if (s0 >= a.stat_split) break;
-            request(a, s0);
+            request();
         }
         const unsigned sum_at = scratch + (unsigned)tid_x() * 8, m_at = scratch + THREADS * 8 + (unsigned)tid_x() * 4;
         asm volatile("ds_write_b64 %0, %1\n\tds_write_b32 %2, %3" ::"v"(sum_at), "v"(sum), "v"(m_at), "v"(M) : "memory");
