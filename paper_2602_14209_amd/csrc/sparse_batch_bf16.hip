@@ -30,43 +30,12 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
-#include "lds_asm.hpp"
-#include "ids.hpp"
-#include "plan.hpp"
+#include "sparse_batch.hpp"
 
 namespace mage {
 
-typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
-typedef float f32x4_t __attribute__((ext_vector_type(4)));
-typedef unsigned short u16;
-
-constexpr int SB_WAVES = 8;
 constexpr int SB_ROWS = SB_WAVES * 16;       // query rows per workgroup
-constexpr int SB_TK = 32;                    // keys per tile (two 16-key MFMA blocks)
 constexpr int SB_NBUF = 4;                   // ring slots
-constexpr int SB_IDX_TILES = 64;             // tiles whose index entries LDS holds at a time (2048 entries)
-
-// What the kernel needs of a call, packed: the kernel arguments arrive through scalar loads that the very
-// first instructions wait for, so they are few and adjacent, and what the host can work out is worked out
-// there (the divisions by Hkv and B become a multiply-high).
-struct BatchArgs {
-    const void *q, *kc, *vc, *kblk, *vblk;
-    const int32_t *idx;
-    float *out, *lse_out;
-    long long seq_q, seq_kv, seq_idx, seq_blk, seq_out, seq_lse;   // element strides between sequences
-    int B, Hq, Hkv, G, R;
-    int nk, n_blk;               // selected cache rows, the block's own rows (0 = none)
-    int n_units;                 // n_seq * Hkv
-    unsigned inv_Hkv;            // ceil(2^32 / Hkv) for Hkv >= 2: unit / Hkv == mulhi(unit, inv_Hkv) while unit * Hkv < 2^32
-    unsigned inv_B;              // the same for B (row * B < 2^32)
-    float scale_log2;
-};
-
-constexpr int SB_GRID_Y = 32768;            // workgroup id: x = place inside a block of ids, (z, y) = block (y < SB_GRID_Y)
-
-// XOR swizzle of the 16-byte chunk index of tile row r (taken modulo 16): the 16 rows of a K fragment
-// read and the 8 rows of one phase of a transposing V read land on distinct LDS banks.
-__device__ __forceinline__ int sb_swz(int r) { return ((r & 7) << 1) | ((r >> 3) & 1); }
 
 // Tile t has landed once at most N younger row requests of this wavefront are in flight; every LDS read issued so far
 // has returned.  a, b: the index-entry registers (the same one twice where a wavefront has a single entry).
@@ -423,6 +392,7 @@ hipError_t bf16_sparse_batched(const KernelArgs &k, int d, int row_groups, int n
     a.inv_Hkv = k.Hkv >= 2 ? (unsigned)(((1ull << 32) + k.Hkv - 1) / k.Hkv) : 0u;
     a.inv_B = k.B >= 2 ? (unsigned)(((1ull << 32) + k.B - 1) / k.B) : 0u;
     a.scale_log2 = k.scale_log2;
+    if (const int rw = sparse_few_row_tiles(n_units, k.R, a.nk + a.n_blk)) return launch_sparse_few(a, d, rw, stream);
     const unsigned gy = (unsigned)(n_blocks < SB_GRID_Y ? n_blocks : SB_GRID_Y);
     const unsigned gz = (unsigned)((n_blocks + SB_GRID_Y - 1) / SB_GRID_Y);
     dim3 grid(8 * row_groups, gy, gz), block(SB_WAVES * 64);
