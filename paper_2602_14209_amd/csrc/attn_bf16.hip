@@ -274,6 +274,22 @@ template <int D>
 __device__ __forceinline__ void load_q_frag(const KernelArgs &a, const u16 *q, int h, int row, bf16x8_t (&qf)[D / 16])
 {
     const int lg = (tid_x() & 63) >> 5;
+    if constexpr (D == 256) {
+        // 256 channels are a page estimate's [max | min] rows of d = 128: the query is split by sign, [max(q, 0) | min(q, 0)]
+        const int r = row < a.R ? row : a.R - 1;          // (what rows past the last compute is never used)
+        const int gl = row_group(a, r), qi = r - gl * a.B;
+        const u16 *src = q + ((long long)qi * a.Hq + (long long)h * a.G + gl) * 128 + 8 * lg;
+#pragma unroll
+        for (int ks = 0; ks < 8; ++ks) {
+            const u32x4_t x = *reinterpret_cast<const u32x4_t *>(src + ks * 16);
+            u32x4_t neg;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) neg[i] = x[i] & (((x[i] >> 15) & 0x00010001u) * 0xffffu);
+            qf[ks] = __builtin_bit_cast(bf16x8_t, x ^ neg);
+            qf[8 + ks] = __builtin_bit_cast(bf16x8_t, neg);
+        }
+        return;
+    }
     if (row < a.R) {
         const int gl = row_group(a, row), qi = row - gl * a.B;
         const u16 *src = q + ((long long)qi * a.Hq + (long long)h * a.G + gl) * D + 8 * lg;
@@ -372,6 +388,10 @@ void attn_bf16_kernel(const KernelArgs a)
     const int row = row0 + l32;
     const bool wave_active = row0 < a.R;
 
+    // kernel arguments that only the epilogue needs are fetched up front: no scalar load may share the counter with the
+    // fragment reads of the loop
+    float *const part_m = a.part_m, *const part_l = a.part_l;
+    if constexpr (MODE == MODE_STATS) asm volatile("" ::"s"(part_m), "s"(part_l));
     const SplitRange sr = split_range(a, split);
     const int ntiles = sr.cache_tiles + sr.blk_tiles;
 
@@ -676,8 +696,8 @@ void attn_bf16_kernel(const KernelArgs a)
     if (MODE == MODE_STATS) {
         if (owner && row < a.R && lg == 0) {
             const long long pi = ((long long)h * a.n_split + split) * a.rpad + row;
-            a.part_m[pi] = m_run;
-            a.part_l[pi] = l_tot;
+            part_m[pi] = m_run;
+            part_l[pi] = l_tot;
         }
         return;
     }

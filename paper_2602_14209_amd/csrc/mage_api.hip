@@ -26,7 +26,8 @@ hipError_t launch_quest_query(const void *q, void *q2, long long rows, int d, hi
 hipError_t launch_expand_pages(const int32_t *pages, int32_t *idx, int Hkv, int k, int p, hipStream_t stream);
 hipError_t launch_overlap(const int32_t *a, const int32_t *b, int n_rows, int k, int a_rows, float *out, hipStream_t stream);
 hipError_t launch_topk(const float *alpha, const float *group_max, int Hkv, long long L, int k, int32_t *idx_out, const RescoreArgs &rs,
-                       const KernelArgs *comb, int d, hipStream_t stream);
+                       int page, const KernelArgs *comb, int d, hipStream_t stream);
+bool topk_expands(long long L, int k);
 }  // namespace mage
 
 using namespace mage;
@@ -58,6 +59,7 @@ RescoreArgs rescore_args(const mage_shape &s, const KernelArgs &a, const float *
     r.n_split = n_split;
     r.rpad = rpad;
     r.scale_log2 = scale_log2;
+    r.split_q = s.d == 256;
     r.inv_rows = 1.0 / ((double)r.R * (double)key_weight);
     r.eps = kNearTieBand;
     return r;
@@ -214,8 +216,8 @@ int run_sparse_bf16(const mage_shape *shape, bool compact, int n_seq, const void
 
 // The selection pipeline (row statistics, log-sum-exp, column sums, top-k) on a validated
 // geometry.  `scale_log2` = log2(e) times the factor on the logit; `key_weight`: every key stands for
-// that many positions of equal score (its probability is shared among them); shape->d may be 256
-// here (page-summary rows).
+// that many positions of equal score (its probability is shared among them); shape->d may be 256 here (page-summary rows;
+// q1 then has 128 channels, which the kernels split by sign).  page > 1: idx_out receives that many positions per selected key.
 // Launch-free argument check of the selection pipeline (everything select_impl can reject).
 int select_check(const mage_shape *shape, const void *q1, const void *k_cache,
                  const int32_t *idx_out, const float *alpha_out, const float *pbar_out,
@@ -229,7 +231,7 @@ int select_check(const mage_shape *shape, const void *q1, const void *k_cache,
     return MAGE_OK;
 }
 
-int select_impl(const mage_shape *shape, float scale_log2, int key_weight, const void *q1, const void *k_cache,
+int select_impl(const mage_shape *shape, float scale_log2, int key_weight, int page, const void *q1, const void *k_cache,
                 int32_t *idx_out, float *alpha_out, float *pbar_out,
                 void *workspace, size_t workspace_bytes, void *hip_stream)
 {
@@ -275,7 +277,7 @@ int select_impl(const mage_shape *shape, float scale_log2, int key_weight, const
         if (e != hipSuccess) return MAGE_ERR_HIP;
         e = launch_topk(a.alpha, a.gmax, shape->Hkv, shape->L, shape->k, idx_out,
                         rescore_args(*shape, a, a.part_m, a.part_l, p.n_split, p.rpad, scale_log2, key_weight),
-                        nullptr, shape->d, stream);
+                        page, nullptr, shape->d, stream);
         if (e != hipSuccess) return MAGE_ERR_HIP;
     }
     if (pbar_out) {                                  // the same sums restricted to the B rows of one query head at a time
@@ -331,7 +333,7 @@ int mage_select(const mage_shape *shape, const void *q1, const void *k_cache,
 {
     const int rc = check_shape(shape, true);
     if (rc != MAGE_OK) return rc;
-    return select_impl(shape, (float)(1.4426950408889634 / sqrt((double)shape->d)), 1, q1, k_cache, idx_out, alpha_out, nullptr,
+    return select_impl(shape, (float)(1.4426950408889634 / sqrt((double)shape->d)), 1, 1, q1, k_cache, idx_out, alpha_out, nullptr,
                        workspace, workspace_bytes, hip_stream);
 }
 
@@ -383,7 +385,7 @@ int mage_select_static(const mage_shape *shape, const void *q1, const void *k_ca
     if (ra != MAGE_OK) return ra;
     void *ws = static_scratch();
     if (!ws) return MAGE_ERR_HIP;
-    return select_impl(shape, (float)(1.4426950408889634 / sqrt((double)shape->d)), 1, q1, k_cache, idx_out, alpha_out, nullptr,
+    return select_impl(shape, (float)(1.4426950408889634 / sqrt((double)shape->d)), 1, 1, q1, k_cache, idx_out, alpha_out, nullptr,
                        ws, kStaticScratchBytes, hip_stream);
 }
 
@@ -393,7 +395,7 @@ int mage_block_probs(const mage_shape *shape, const void *q1, const void *k_cach
     const int rc = check_shape(shape, true);
     if (rc != MAGE_OK) return rc;
     if (!pbar_out) return MAGE_ERR_NULL;
-    return select_impl(shape, (float)(1.4426950408889634 / sqrt((double)shape->d)), 1, q1, k_cache, nullptr, nullptr, pbar_out,
+    return select_impl(shape, (float)(1.4426950408889634 / sqrt((double)shape->d)), 1, 1, q1, k_cache, nullptr, nullptr, pbar_out,
                        workspace, workspace_bytes, hip_stream);
 }
 
@@ -444,7 +446,7 @@ int mage_step1(const mage_shape *shape, const void *q1, const void *k_cache, con
     // the split partials of the attention are merged beside the top-k, which leaves nearly the whole chip idle
     if (launch_topk(a.alpha, a.gmax, shape->Hkv, shape->L, shape->k, idx_out,
                     rescore_args(*shape, a, stat_m, stat_l, pa.n_split, pa.rpad, a.scale_log2, 1),
-                    pa.n_split > 1 ? &comb : nullptr, shape->d, stream) != hipSuccess)
+                    1, pa.n_split > 1 ? &comb : nullptr, shape->d, stream) != hipSuccess)
         return MAGE_ERR_HIP;
     return MAGE_OK;
 }
@@ -584,12 +586,13 @@ int mage_quest_select(const mage_shape *shape, int p, const void *q, const void 
     int32_t *pages = reinterpret_cast<int32_t *>(w + lay.pages);
     const int rv = select_check(&s2, q2, summary, pages, est_out, nullptr, w + lay.select, lay.pages - lay.select);
     if (rv != MAGE_OK) return rv;                    // nothing has been launched yet
-    if (launch_quest_query(q, q2, (long long)shape->B * shape->Hq, shape->d, stream) != hipSuccess) return MAGE_ERR_HIP;
+    const bool split_here = s2.d == 256, expand = p > 1 && !topk_expands(s2.L, s2.k);
+    if (!split_here && launch_quest_query(q, q2, (long long)shape->B * shape->Hq, shape->d, stream) != hipSuccess) return MAGE_ERR_HIP;
     // the bound is scaled like a logit of the original head dimension
-    const int rs = select_impl(&s2, (float)(1.4426950408889634 / sqrt((double)shape->d)), p, q2, summary, pages, est_out, nullptr,
-                               w + lay.select, lay.pages - lay.select, hip_stream);
+    const int rs = select_impl(&s2, (float)(1.4426950408889634 / sqrt((double)shape->d)), p, expand ? 1 : p, split_here ? q : q2, summary,
+                               expand ? pages : idx_out, est_out, nullptr, w + lay.select, lay.pages - lay.select, hip_stream);
     if (rs != MAGE_OK) return rs;
-    if (launch_expand_pages(pages, idx_out, shape->Hkv, shape->k, p, stream) != hipSuccess) return MAGE_ERR_HIP;
+    if (expand && launch_expand_pages(pages, idx_out, shape->Hkv, shape->k, p, stream) != hipSuccess) return MAGE_ERR_HIP;
     return MAGE_OK;
 }
 

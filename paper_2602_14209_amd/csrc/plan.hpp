@@ -218,6 +218,7 @@ struct RescoreArgs {
     int esz;                         // bytes per element of q / kc: 2 (bf16) or 4 (fp32)
     int d, Hq, Hkv, G, B, R, n_split, rpad;
     float scale_log2;                // the factor the statistics were taken with
+    int split_q;                     // q has d / 2 channels, to be split by sign into [max(q, 0) | min(q, 0)]
     double inv_rows;                 // 1 / (R * key weight)
     float eps;
 };

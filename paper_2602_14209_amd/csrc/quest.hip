@@ -6,7 +6,8 @@
 // max(q*a, q*b) with a >= b is q*a for q >= 0 and q*b for q < 0, so the score is the dot product of
 // [max(q,0) | min(q,0)] with the page's row [Kmax | Kmin] of length 2d.  The summaries are
 // therefore stored as such rows, the queries are split here, and the scoring, the softmax over
-// pages and the block/group average run on the MFMA selection kernels with head dimension 2d.
+// pages and the block/group average run on the MFMA selection kernels with head dimension 2d.  At d = 128 those kernels
+// (instantiated for 256 channels, which nothing else uses) split the queries themselves while they load them.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include "ids.hpp"
@@ -58,7 +59,8 @@ __global__ __launch_bounds__(256) void page_summary_kernel(const unsigned char *
     *reinterpret_cast<uint4 *>(row + (long long)d * ESZ) = make_uint4(wn[0], wn[1], wn[2], wn[3]);
 }
 
-// q2[q][g][0:d] = max(q, 0), q2[q][g][d:2d] = min(q, 0)   (bf16 bit patterns; -0 counts as negative)
+// q2[q][g][0:d] = max(q, 0), q2[q][g][d:2d] = min(q, 0)   (bf16 bit patterns; -0 counts as negative): for d = 64, whose
+// doubled rows go through kernels that ordinary selection uses too
 __global__ __launch_bounds__(256) void quest_query_kernel(const uint16_t *__restrict__ q, uint16_t *__restrict__ q2, long long rows, int d)
 {
     const long long t = (long long)wg_x() * 256 + tid_x();
@@ -71,6 +73,7 @@ __global__ __launch_bounds__(256) void quest_query_kernel(const uint16_t *__rest
     q2[r * 2 * d + d + c] = neg ? v : (uint16_t)0;
 }
 
+// Where the top-k does not expand the pages itself (more than TK_FILTER_MAX_K of them, or a row longer than its bitmap):
 // idx[h][i] = pages[h][i / p] * p + i % p: the positions of the selected pages, ascending when the pages are
 __global__ __launch_bounds__(256) void expand_pages_kernel(const int32_t *__restrict__ pages, int32_t *__restrict__ idx, int Hkv, int k, int p)
 {
@@ -81,22 +84,32 @@ __global__ __launch_bounds__(256) void expand_pages_kernel(const int32_t *__rest
 }
 
 // out[i] = |A_(i % a_rows) intersect B_i| / k.  Rows of `a` ascending (binary search), rows of `b` in any order.
+// STAGED: the row of `a` is searched in LDS.  The search is a chain of log2(k) dependent reads, 0.35 us each from the
+// cache: k = 512 takes 5.9 us that way, 4.1 us with the row in LDS (most of it launch and two round trips).
+template <bool STAGED>
 __global__ __launch_bounds__(256) void overlap_kernel(const int32_t *__restrict__ a, const int32_t *__restrict__ b, int k, int a_rows,
                                                       float *__restrict__ out)
 {
     __shared__ int part[4];
+    extern __shared__ int32_t row[];
     const int i = wg_x();
     const int32_t *ar = a + (long long)(i % a_rows) * k, *br = b + (long long)i * k;
+    int32_t v = tid_x() < (unsigned)k ? br[tid_x()] : 0;
+    if (STAGED) {
+        for (int e = tid_x(); e < k; e += 256) row[e] = ar[e];
+        __syncthreads();
+    }
     int cnt = 0;
     for (int e = tid_x(); e < k; e += 256) {
-        const int32_t v = br[e];
-        int lo = 0, hi = k;                 // first position with ar[pos] >= v
+        const int32_t next = e + 256 < k ? br[e + 256] : 0;
+        int lo = 0, hi = k;                 // first position with a[pos] >= v
         while (lo < hi) {
             const int mid = (lo + hi) >> 1;
-            if (ar[mid] < v) lo = mid + 1;
+            if ((STAGED ? row[mid] : ar[mid]) < v) lo = mid + 1;
             else hi = mid;
         }
-        cnt += (lo < k && ar[lo] == v) ? 1 : 0;
+        cnt += (lo < k && (STAGED ? row[lo] : ar[lo]) == v) ? 1 : 0;
+        v = next;
     }
 #pragma unroll
     for (int dlt = 32; dlt >= 1; dlt >>= 1) cnt += __shfl_xor(cnt, dlt);
@@ -133,7 +146,9 @@ hipError_t launch_expand_pages(const int32_t *pages, int32_t *idx, int Hkv, int 
 
 hipError_t launch_overlap(const int32_t *a, const int32_t *b, int n_rows, int k, int a_rows, float *out, hipStream_t stream)
 {
-    hipLaunchKernelGGL(overlap_kernel, dim3(n_rows), dim3(256), 0, stream, a, b, k, a_rows, out);
+    constexpr int kStagedMax = 15 * 1024;        // entries: 60 KB of LDS, two workgroups per CU
+    if (k <= kStagedMax) hipLaunchKernelGGL(overlap_kernel<true>, dim3(n_rows), dim3(256), k * sizeof(int32_t), stream, a, b, k, a_rows, out);
+    else hipLaunchKernelGGL(overlap_kernel<false>, dim3(n_rows), dim3(256), 0, stream, a, b, k, a_rows, out);
     return hipGetLastError();
 }
 

@@ -246,13 +246,18 @@ __device__ __forceinline__ void rescore_candidates(const RescoreArgs &rs, int h,
         }
         __syncthreads();
         const int gl = live ? r / rs.B : 0, qi = live ? r - gl * rs.B : 0;
-        const long long qo = ((long long)qi * rs.Hq + (long long)h * rs.G + gl) * rs.d + part * cpt;
+        // split_q: the queries are rows of d / 2 channels, to be taken as [max(q, 0) | min(q, 0)]
+        const long long qo = ((long long)qi * rs.Hq + (long long)h * rs.G + gl) * (rs.split_q ? rs.d / 2 : rs.d) + (rs.split_q ? (part & 1) : part) * cpt;
         for (int c = 0; c < n; ++c) {
             const long long j = (long long)list[slot[c]].y;
             const long long ko = (j * rs.Hkv + h) * rs.d + part * cpt;
             double p = 0.0;
             if (live)
-                for (int e = 0; e < cpt; ++e) p = fma(load_elem(rs.q, qo + e, rs.esz), load_elem(rs.kc, ko + e, rs.esz), p);
+                for (int e = 0; e < cpt; ++e) {
+                    double qv = load_elem(rs.q, qo + e, rs.esz);
+                    if (rs.split_q) qv = part < 2 ? fmax(qv, 0.0) : fmin(qv, 0.0);
+                    p = fma(qv, load_elem(rs.kc, ko + e, rs.esz), p);
+                }
             p += __shfl_xor(p, 1);
             p += __shfl_xor(p, 2);
             double t = (live && part == 0) ? exp2(p * (double)rs.scale_log2 - (double)rowM[rl]) / rowL[rl] : 0.0;
@@ -305,9 +310,10 @@ __device__ __forceinline__ uint32_t walk_bitmap(const uint32_t *bits, int n, uin
 // DC: head dimension of attention partials that the workgroups from n_heads on merge (four query rows each), 0 = none.
 // In the fused step 1 that merge (5 to 8 us as a launch of its own) depends on nothing but the attention pass and runs
 // beside the top-k's few workgroups.
-template <int DC>
+// PAGED: every selected element stands for `page` consecutive positions, which are what is written.
+template <int DC, bool PAGED>
 __global__ __launch_bounds__(TK_THREADS) void topk_kernel(const float *alpha, const float *group_max, long long L, int k, int32_t *idx_out,
-                                                          const RescoreArgs rs, int n_heads, const KernelArgs comb)
+                                                          const RescoreArgs rs, int page, int n_heads, const KernelArgs comb)
 {
     if constexpr (DC > 0) {
         __shared__ CombineLds<DC> comb_lds[TK_THREADS / 256];
@@ -325,7 +331,7 @@ __global__ __launch_bounds__(TK_THREADS) void topk_kernel(const float *alpha, co
     __shared__ uint32_t tmp2[TK_WAVES + 1];
     __shared__ uint32_t bcast[3];                        // radix route: chosen digit, rank inside its bucket, bucket size
     __shared__ uint32_t glist[TK_HITS];                  // filter route: groups at or above the bound
-    __shared__ uint32_t winners[TK_FILTER_MAX_K];        // positions in the set, for rows longer than the bitmap
+    __shared__ uint32_t winners[TK_FILTER_MAX_K];        // the set: for rows longer than the bitmap (unordered), or to be expanded to positions (ascending)
     __shared__ uint2 list[TK_LIST];                      // (value, position) around rank k
     __shared__ uint32_t ltake[TK_LIST];
     __shared__ uint32_t n_hit, n_cand, n_win, n_list, n_near, n_near_in, thr_bits, next_bits;
@@ -336,7 +342,20 @@ __global__ __launch_bounds__(TK_THREADS) void topk_kernel(const float *alpha, co
 
     const int h = wg_x();
     const uint32_t *u = reinterpret_cast<const uint32_t *>(alpha) + (long long)h * L;
-    int32_t *out = idx_out + (long long)h * k;
+    int32_t *out = idx_out + (long long)h * k * (PAGED ? page : 1);
+    auto put = [&](uint32_t rank, int j) {
+        if (PAGED) winners[rank] = (uint32_t)j;
+        else out[rank] = j;
+    };
+    // a set of pages: every position of each of them (the caller keeps k <= TK_FILTER_MAX_K and L <= TK_BITMAP then)
+    auto expand = [&] {
+        if (!PAGED) return;
+        __syncthreads();
+        for (int i = tid_x(); i < k * page; i += TK_THREADS) {
+            const int r = i / page;
+            out[i] = (int32_t)winners[r] * page + (i - r * page);
+        }
+    };
     const int ng = (int)((L + kGroupKeys - 1) / kGroupKeys);          // group maxima of the row
     // a row of one sweep is binned directly; so is a longer one whose groups would mostly pass the filter
     const bool filter = L > TK_SWEEP && k <= ng / 4 && k <= TK_FILTER_MAX_K;
@@ -590,8 +609,9 @@ __global__ __launch_bounds__(TK_THREADS) void topk_kernel(const float *alpha, co
             }
             if (L <= TK_BITMAP) {
                 walk_bitmap(bits, (int)L, 0u, tmp2, [&](uint32_t rank, int j) {
-                    if (rank < (uint32_t)k) out[rank] = j;
+                    if (rank < (uint32_t)k) put(rank, j);
                 });
+                expand();
                 return;
             }
             // rows longer than the bitmap: one stretch of positions after the other
@@ -650,10 +670,10 @@ __global__ __launch_bounds__(TK_THREADS) void topk_kernel(const float *alpha, co
         for (int i = 0; i < TK_EPT; ++i) {
             if (j0 + i < L) {
                 if (x[i] > thr) {
-                    out[g + (e < want ? e : want)] = (int32_t)(j0 + i);
+                    put(g + (e < want ? e : want), (int)(j0 + i));
                     ++g;
                 } else if (x[i] == thr) {
-                    if (e < want) out[g + e] = (int32_t)(j0 + i);
+                    if (e < want) put(g + e, (int)(j0 + i));
                     ++e;
                 }
             }
@@ -661,23 +681,29 @@ __global__ __launch_bounds__(TK_THREADS) void topk_kernel(const float *alpha, co
         base_gt += tot_gt;
         base_eq += tot_eq;
     }
+    expand();
 }
 
 // group_max: [Hkv][ceil(L / kGroupKeys)] maxima of alpha over groups of kGroupKeys consecutive positions
+// Can the top-k expand a set of k pages out of L to positions itself?
+bool topk_expands(long long L, int k) { return k <= TK_FILTER_MAX_K && L <= TK_BITMAP; }
+
+// page: 1, or the number of consecutive positions every selected element stands for: idx_out is then [Hkv][k * page].
 // comb: nullptr, or the arguments of an attention call (head dimension d) whose split partials are merged in the same launch
 hipError_t launch_topk(const float *alpha, const float *group_max, int Hkv, long long L, int k, int32_t *idx_out, const RescoreArgs &rs,
-                       const KernelArgs *comb, int d, hipStream_t stream)
+                       int page, const KernelArgs *comb, int d, hipStream_t stream)
 {
     dim3 grid(Hkv), block(TK_THREADS);
     if (!comb) {
-        hipLaunchKernelGGL(topk_kernel<0>, grid, block, 0, stream, alpha, group_max, L, k, idx_out, rs, Hkv, KernelArgs{});
+        if (page > 1) hipLaunchKernelGGL((topk_kernel<0, true>), grid, block, 0, stream, alpha, group_max, L, k, idx_out, rs, page, Hkv, KernelArgs{});
+        else hipLaunchKernelGGL((topk_kernel<0, false>), grid, block, 0, stream, alpha, group_max, L, k, idx_out, rs, 1, Hkv, KernelArgs{});
         return hipGetLastError();
     }
     const long long rows = (long long)comb->R * Hkv, per = TK_THREADS / 256;
     if ((rows + per - 1) / per + Hkv > 0x7fffffff) return hipErrorInvalidValue;
     grid.x = Hkv + (unsigned)((rows + per - 1) / per);
-    if (d == 128) hipLaunchKernelGGL(topk_kernel<128>, grid, block, 0, stream, alpha, group_max, L, k, idx_out, rs, Hkv, *comb);
-    else if (d == 64) hipLaunchKernelGGL(topk_kernel<64>, grid, block, 0, stream, alpha, group_max, L, k, idx_out, rs, Hkv, *comb);
+    if (d == 128) hipLaunchKernelGGL((topk_kernel<128, false>), grid, block, 0, stream, alpha, group_max, L, k, idx_out, rs, 1, Hkv, *comb);
+    else if (d == 64) hipLaunchKernelGGL((topk_kernel<64, false>), grid, block, 0, stream, alpha, group_max, L, k, idx_out, rs, 1, Hkv, *comb);
     else return hipErrorInvalidValue;
     return hipGetLastError();
 }
