@@ -12,7 +12,7 @@
 // exactly, all pairs at once.  Two routes:
 //   direct route: the row is binned element by element, then classified.  For rows that one sweep of registers
 //     holds (L <= 16384), and for large k, where a filter would let most of the row through.
-//   filter route (long rows, k <= L / 64): the k-th largest of the maxima of disjoint groups of elements is a lower bound
+//   filter route (long rows, k up to three quarters of the groups): the k-th largest of the maxima of disjoint groups of elements is a lower bound
 //     of the k-th largest element.  The column-sum pass leaves one maximum per kGroupKeys consecutive keys; they are
 //     binned first and only the groups at or above the bound (about k of them) are read at all.
 // Membership is kept as a bitmap in LDS; walking it gives the positions in ascending order.
@@ -358,7 +358,7 @@ __global__ __launch_bounds__(TK_THREADS) void topk_kernel(const float *alpha, co
     };
     const int ng = (int)((L + kGroupKeys - 1) / kGroupKeys);          // group maxima of the row
     // a row of one sweep is binned directly; so is a longer one whose groups would mostly pass the filter
-    const bool filter = L > TK_SWEEP && k <= ng / 4 && k <= TK_FILTER_MAX_K;
+    const bool filter = L > TK_SWEEP && k <= ng - ng / 4 && k <= TK_FILTER_MAX_K;
 
     if (filter || L <= TK_BITMAP) {
         const int t = tid_x(), lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
