@@ -8,8 +8,7 @@
 // phase costs 16 issue cycles) plus the round trips to memory.  Hence ONE histogram instead of a radix select: alpha is a
 // probability, so its useful range is known beforehand and a bin is a fixed interval of the fp32 bit pattern
 // (value_bin: 64 octaves below 1.0, 64 bins per octave).  Everything above the bin that holds rank k is in, and only
-// the few elements of that bin and its two neighbours (1.6 % of a value each, typically 10 .. 100 elements) are ranked
-// exactly, all pairs at once.  Two routes:
+// the few elements of that bin (1.6 % of a value, typically 5 .. 50 elements) are ranked exactly, all pairs at once.  Two routes:
 //   direct route: the row is binned element by element, then classified.  For rows that one sweep of registers
 //     holds (L <= 16384), and for large k, where a filter would let most of the row through.
 //   filter route (long rows, k up to three quarters of the groups): the k-th largest of the maxima of disjoint groups of elements is a lower bound
@@ -48,6 +47,8 @@ constexpr int TK_HITS = 4096;                        // filter route: groups at 
 constexpr int TK_NX = 4;                             // filter route: 16-byte pieces of those groups that a thread keeps in registers
 constexpr int TK_FILTER_MAX_K = 2048;
 constexpr int TK_LIST = 512;                         // elements around rank k that are ranked all pairs
+constexpr uint32_t TK_MARGIN = 256;                  // the list reaches this many bit patterns past the bin of rank k: more than
+                                                     // the near-tie band on either side (a pattern is at least 2^-24 of a value)
 constexpr int TK_BITMAP = 262144;                    // positions whose membership bits LDS holds
 constexpr int TK_NEAR_MAX = 32;                      // candidates re-scored at most; more of them (massive ties) keep the fp32 ranking
 
@@ -278,32 +279,45 @@ __device__ __forceinline__ void rescore_candidates(const RescoreArgs &rs, int h,
     __syncthreads();
 }
 
-// Bits [0, n) of the bitmap in ascending order (bits from n to the next multiple of 16 are zero): emit(rank, position)
+// Bits [0, n) of the bitmap in ascending order (bits from n to the next multiple of 128 are zero): emit(rank, position)
 // for every set bit, rank counted from `first`; returns the number of set bits.  The caller has put a barrier between
 // the last change of the bitmap and this.
 template <class Emit>
 __device__ __forceinline__ uint32_t walk_bitmap(const uint32_t *bits, int n, uint32_t first, uint32_t *tmp, Emit emit)
 {
-    const uint16_t *half = reinterpret_cast<const uint16_t *>(bits);
-    const int hw = (n + 15) >> 4, per = (hw + TK_THREADS - 1) / TK_THREADS;     // 16 positions at a time, `per` of them per thread
-    uint32_t mine = 0;
-    for (int i = 0; i < per; ++i) {
-        const int w = tid_x() * per + i;
-        if (w < hw) mine += __popc((uint32_t)half[w]);
-    }
-    uint32_t total;
-    uint32_t rank = first + block_scan_incl(mine, tmp, total) - mine;
-    if (mine != 0) {
-        for (int i = 0; i < per; ++i) {
-            const int w = tid_x() * per + i;
-            uint32_t b = w < hw ? half[w] : 0u;
-            while (b) {
-                emit(rank, w * 16 + __ffs(b) - 1);
-                ++rank;
-                b &= b - 1;
+    // Short bitmaps: 16 positions per thread.  Longer ones: whole words, four at a time where there are that many.
+    const int words = (n + 31) >> 5;
+    uint32_t w[4] = {0u, 0u, 0u, 0u};
+    uint32_t total, mine = 0;
+    int at, per;                                          // first word (half word) of this thread, words per thread
+    if (words <= TK_THREADS / 2) {
+        at = tid_x();
+        per = 0;
+        if (at < 2 * words) w[0] = reinterpret_cast<const uint16_t *>(bits)[at];
+        mine = __popc(w[0]);
+    } else {
+        per = (words + TK_THREADS - 1) / TK_THREADS;
+        per = per > 2 ? (per + 3) & ~3 : per;
+        at = tid_x() * per;
+        for (int i = 0; i < per; i += 4) {
+            if (per >= 4) {
+                const uint4 v = at + i < words ? *reinterpret_cast<const uint4 *>(bits + at + i) : make_uint4(0, 0, 0, 0);
+                w[0] = v.x; w[1] = v.y; w[2] = v.z; w[3] = v.w;
+            } else {
+                if (at < words) w[0] = bits[at];
+                if (per == 2 && at + 1 < words) w[1] = bits[at + 1];
             }
+            mine += __popc(w[0]) + __popc(w[1]) + __popc(w[2]) + __popc(w[3]);
         }
     }
+    uint32_t rank = first + block_scan_incl(mine, tmp, total) - mine;
+    if (mine == 0) return total;
+    if (per <= 1) {
+        for (uint32_t b = w[0]; b; b &= b - 1) emit(rank++, at * (per ? 32 : 16) + __ffs(b) - 1);
+        return total;
+    }
+    for (int i = 0; i < per; ++i)
+        for (uint32_t b = at + i < words ? bits[at + i] : 0u; b; b &= b - 1) emit(rank++, (at + i) * 32 + __ffs(b) - 1);
     return total;
 }
 
@@ -440,23 +454,21 @@ __global__ __launch_bounds__(TK_THREADS) void topk_kernel(const float *alpha, co
                 m &= m - 1;
             }
         };
-        uint32_t want;                                    // how many of the listed elements belong to the set
         if (!filter) {
-            want = (uint32_t)k - (before - (bin > 0 ? hist[bin - 1] : 0u));
-            // in: the bins before the neighbourhood of `bin`; listed: `bin` and its two neighbours
+            // in: everything above `bin` and its margin; listed: `bin` and the margins
+            const uint32_t in_floor = bin_floor(bin - 1) + TK_MARGIN, list_floor = bin_floor(bin) - TK_MARGIN;
             for (int j0 = 0; j0 < len && !give_up; j0 += TK_SWEEP) {
                 if (len > TK_SWEEP) sweep(j0);
                 if (j0 + wave * 64 * per < len) {
-                    const uint32_t in = at_least(bin_floor(bin - 2));
-                    append(at_least(bin_floor(bin + 1)) & ~in, j0 + t * per);
+                    const uint32_t in = at_least(in_floor);
+                    append(at_least(list_floor) & ~in, j0 + t * per);
                     if (per == 8) reinterpret_cast<uint8_t *>(bits)[t] = (uint8_t)in;
                     else reinterpret_cast<uint16_t *>(bits)[(j0 >> 4) + t] = (uint16_t)in;
                 }
             }
         } else {
-            // ---- groups at or above the bound: one bin below the k-th largest maximum, so that the neighbours of rank
-            // k's bin are complete
-            const uint32_t floor = bin_floor(bin + 1);
+            // ---- groups at or above the bound (and its margin)
+            const uint32_t floor = bin_floor(bin) - TK_MARGIN;
             for (int j0 = 0; j0 < len && !give_up; j0 += TK_SWEEP) {
                 if (len > TK_SWEEP) sweep(j0);
                 uint32_t m = j0 + wave * 64 * per < len ? at_least(floor) : 0u;
@@ -524,8 +536,7 @@ __global__ __launch_bounds__(TK_THREADS) void topk_kernel(const float *alpha, co
             } else {
                 pick_bin(hist2, (uint32_t)k, lscan, tmp2, bin, before);
             }
-            want = (uint32_t)k - (before - (bin > 0 ? hist2[bin - 1] : 0u));
-            const uint32_t in_floor = bin_floor(bin - 2), list_floor = bin_floor(bin + 1);
+            const uint32_t in_floor = bin_floor(bin - 1) + TK_MARGIN, list_floor = bin_floor(bin) - TK_MARGIN;
             for (int i0 = 0; i0 < items; i0 += TK_NX * TK_THREADS) {
                 if (items > TK_NX * TK_THREADS) fetch(i0);
 #pragma unroll
@@ -557,16 +568,20 @@ __global__ __launch_bounds__(TK_THREADS) void topk_kernel(const float *alpha, co
             for (uint32_t i0 = 0; i0 < nl; i0 += TK_THREADS / 16) {
                 const uint32_t i = i0 + (t >> 4);
                 const uint2 me = list[i < nl ? i : 0];
+                // counted together: the rank (low half) and the listed elements above the bin, which `before` has counted
                 uint32_t rank = 0;
                 for (uint32_t o = t & 15; o < nl; o += 16) {
                     const uint2 other = list[o];
                     rank += other.x > me.x || (other.x == me.x && other.y < me.y);
+                    rank += other.x >= bin_floor(bin - 1) ? 0x10000u : 0u;
                 }
                 constexpr int ROW_ROR = 0x120;            // rotation inside a row of 16 lanes
                 rank += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)rank, ROW_ROR + 1, 0xf, 0xf, true);
                 rank += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)rank, ROW_ROR + 2, 0xf, 0xf, true);
                 rank += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)rank, ROW_ROR + 4, 0xf, 0xf, true);
                 rank += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)rank, ROW_ROR + 8, 0xf, 0xf, true);
+                const uint32_t want = (uint32_t)k - before + (rank >> 16);      // how many of the listed elements belong to the set
+                rank &= 0xffffu;
                 if ((t & 15) == 0 && i < nl) {
                     ltake[i] = rank < want;
                     if (rank + 1 == want) thr_bits = me.x;
