@@ -205,16 +205,47 @@ __device__ __forceinline__ void radix_step(const uint32_t *u, long long n, int s
     __syncthreads();
 }
 
-__device__ __forceinline__ double load_elem(const void *p, long long i, int esz)
+// 2^x in fp64 for x <= 0 or a little above: Taylor series of 2^f, |f| <= 1/2, up to the term below 2^-52
+__device__ __forceinline__ double exp2_f64(double x)
 {
-    if (esz == 2) return (double)__uint_as_float((uint32_t)static_cast<const unsigned short *>(p)[i] << 16);
-    return (double)static_cast<const float *>(p)[i];
+    x = fmax(x, -1100.0);                                // (zero, as far as fp64 goes)
+    const double n = __builtin_rint(x), f = x - n;
+    constexpr double C[13] = {1.0, 0.6931471805599453, 0.24022650695910072, 0.05550410866482158, 0.009618129107628477,      // ln2^k / k!
+                              0.0013333558146428443, 0.0001540353039338161, 1.5252733804059841e-05, 1.321548679014431e-06,
+                              1.01780860092397e-07, 7.054911620801123e-09, 4.4455382718708116e-10, 2.5678435993488206e-11};
+    double p = C[12];
+#pragma unroll
+    for (int k = 11; k >= 0; --k) p = fma(p, f, C[k]);
+    return __builtin_amdgcn_ldexp(p, (int)n);
+}
+
+// sum of q[e] * k[e] over the values of a 16-byte piece (8 bf16 or 4 fp32), in order; side: 0, or +1 / -1 to take only the
+// positive / negative part of q
+__device__ __forceinline__ double dot_piece(const uint4 &q, const uint4 &k, int esz, int side, double p)
+{
+    const uint32_t a[4] = {q.x, q.y, q.z, q.w}, b[4] = {k.x, k.y, k.z, k.w};
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        if (esz == 4) {
+            p = fma((double)__uint_as_float(a[i]), (double)__uint_as_float(b[i]), p);
+            continue;
+        }
+#pragma unroll
+        for (int half = 0; half < 2; ++half) {
+            float x = __uint_as_float(half ? a[i] & 0xffff0000u : a[i] << 16);
+            const float y = __uint_as_float(half ? b[i] & 0xffff0000u : b[i] << 16);
+            x = side > 0 ? fmaxf(x, 0.f) : side < 0 ? fminf(x, 0.f) : x;
+            p = fma((double)x, (double)y, p);            // (a product in fp32 would be exact too, but for underflow)
+        }
+    }
+    return p;
 }
 
 // alpha[h, j] in fp64 from the inputs (Eq. 5) for n of the listed elements, j = list[slot[c]].y:
 //   1/(G*B) * sum over the R rows of exp2(q_r.k_j * scale - M_r) / L_r,
 // with (M_r, L_r) the row's softmax statistics merged in fp64 over the key splits.  Four threads per
-// row (a quarter of the channels and of the splits each), 256 rows per pass.  Every thread of the
+// row (a quarter of the channels and of the splits each), 256 rows per pass.  Taken by one head in a few hundred, and then
+// as a tail of the whole selection: with element-by-element loads and the library's exp2 it took 42 us, 14 us now (two candidates, 224 rows).  Every thread of the
 // workgroup calls; out[c] receives the results rounded to fp32 (valid after the final barrier).
 __device__ __forceinline__ void rescore_candidates(const RescoreArgs &rs, int h, const uint2 *list, const uint32_t *slot, int n, float *out,
                                    float *rowM, double *rowL, double *acc, double *red)
@@ -227,19 +258,42 @@ __device__ __forceinline__ void rescore_candidates(const RescoreArgs &rs, int h,
     for (int r0 = 0; r0 < rs.R; r0 += ROWS) {              // uniform trip count (one pass unless R > 256)
         const int r = r0 + rl;
         const bool live = r < rs.R;
-        // this row's statistics, merged over the key splits
-        float M = -INFINITY;
-        const long long base = (long long)h * rs.n_split * rs.rpad + (live ? r : 0);
-        for (int s = part; s < rs.n_split; s += 4) M = fmaxf(M, rs.stat_m[base + (long long)s * rs.rpad]);
-        M = fmaxf(M, __shfl_xor(M, 1));
-        M = fmaxf(M, __shfl_xor(M, 2));
+        // this row's statistics, merged over the key splits, eight in flight per thread
+        constexpr int SF = 8;
+        float M = -3.0e38f;
         double Lr = 0.0;
-        for (int s = part; s < rs.n_split; s += 4) {
-            const long long pi = base + (long long)s * rs.rpad;
-            Lr += (double)rs.stat_l[pi] * exp2((double)rs.stat_m[pi] - (double)M);
+        const long long base = (long long)h * rs.n_split * rs.rpad + (live ? r : 0);
+        for (int s0 = part; s0 < rs.n_split; s0 += 4 * SF) {
+            float m[SF], l[SF], top = M;
+#pragma unroll
+            for (int i = 0; i < SF; ++i) {
+                const int s = s0 + 4 * i;
+                const long long pi = base + (long long)(s < rs.n_split ? s : s0) * rs.rpad;
+                m[i] = rs.stat_m[pi];
+                l[i] = s < rs.n_split ? rs.stat_l[pi] : 0.f;
+            }
+#pragma unroll
+            for (int i = 0; i < SF; ++i) top = fmaxf(top, m[i]);
+            Lr *= exp2_f64((double)M - (double)top);
+            M = top;
+#pragma unroll 1
+            for (int i = 0; i < SF; ++i) {               // (rolled: the registers rotate)
+                Lr += (double)l[0] * exp2_f64((double)m[0] - (double)M);
+#pragma unroll
+                for (int e = 0; e + 1 < SF; ++e) {
+                    m[e] = m[e + 1];
+                    l[e] = l[e + 1];
+                }
+            }
         }
-        Lr += __shfl_xor(Lr, 1);
-        Lr += __shfl_xor(Lr, 2);
+#pragma unroll
+        for (int d = 1; d <= 2; d <<= 1) {               // the four threads of the row
+            const float mo = __shfl_xor(M, d);
+            const double lo = __shfl_xor(Lr, d);
+            const float top = fmaxf(M, mo);
+            Lr = Lr * exp2_f64((double)M - (double)top) + lo * exp2_f64((double)mo - (double)top);
+            M = top;
+        }
         __syncthreads();                                   // the previous pass is done with rowM / rowL
         if (part == 0) {
             rowM[rl] = M;
@@ -253,15 +307,18 @@ __device__ __forceinline__ void rescore_candidates(const RescoreArgs &rs, int h,
             const long long j = (long long)list[slot[c]].y;
             const long long ko = (j * rs.Hkv + h) * rs.d + part * cpt;
             double p = 0.0;
-            if (live)
-                for (int e = 0; e < cpt; ++e) {
-                    double qv = load_elem(rs.q, qo + e, rs.esz);
-                    if (rs.split_q) qv = part < 2 ? fmax(qv, 0.0) : fmin(qv, 0.0);
-                    p = fma(qv, load_elem(rs.kc, ko + e, rs.esz), p);
-                }
+            const uint4 *qp = reinterpret_cast<const uint4 *>(static_cast<const char *>(rs.q) + qo * rs.esz);
+            const uint4 *kp = reinterpret_cast<const uint4 *>(static_cast<const char *>(rs.kc) + ko * rs.esz);
+            const int side = !rs.split_q ? 0 : part < 2 ? 1 : -1;
+            const int pieces = cpt * rs.esz / 16;        // 2, 4 or 8
+            for (int i = 0; i < pieces; i += 2) {        // (rows past the last read row 0)
+                const uint4 q0 = qp[i], q1 = qp[i + 1], k0 = kp[i], k1 = kp[i + 1];
+                p = dot_piece(q0, k0, rs.esz, side, p);
+                p = dot_piece(q1, k1, rs.esz, side, p);
+            }
             p += __shfl_xor(p, 1);
             p += __shfl_xor(p, 2);
-            double t = (live && part == 0) ? exp2(p * (double)rs.scale_log2 - (double)rowM[rl]) / rowL[rl] : 0.0;
+            double t = (live && part == 0) ? exp2_f64(p * (double)rs.scale_log2 - (double)rowM[rl]) / rowL[rl] : 0.0;
 #pragma unroll
             for (int d = 32; d >= 1; d >>= 1) t += __shfl_xor(t, d);
             __syncthreads();                               // red may still be read from the previous candidate
