@@ -46,8 +46,6 @@ typedef unsigned short u16;
 
 constexpr int SP_WAVES = 8;
 constexpr int SP_KT = 16;          // key positions per tile
-constexpr int SP_TPW = 5;          // tiles per wavefront per pass (register arrays)
-constexpr int SP_MAXT = SP_WAVES * SP_TPW;   // tiles per pass: all of LDS holds V (640 key positions at d=128)
 
 // The compiler may not read, copy or move these registers across this point (they are the
 // destinations of loads it does not know about).
@@ -82,13 +80,20 @@ struct SparseArgs {
 };
 
 // COMPACT: the k cache positions are rows 0..k-1 of a compacted cache (no index set to read).
+// SP_TPW: tiles per wavefront and pass (register arrays; nearly all are loaded whether the wavefront has that many or
+// not, so a call takes the smallest that holds its keys in one pass).
 // DS: the output channels of a row tile are dealt to DS workgroups.  Each of them computes the
 // full scores (every K row, all D channels) but fetches and multiplies only its D/DS channels of
 // V: no result crosses workgroups, the softmax statistics are simply computed DS times, and a
 // compute unit has 1/DS of the V bytes to pull through its memory path.
-template <int D, int DS, bool COMPACT>
+template <int D, int DS, int SP_TPW, bool COMPACT>
 __global__ __launch_bounds__(SP_WAVES * 64) __attribute__((amdgpu_waves_per_eu(2))) void sparse_bf16_kernel(const SparseArgs a)
 {
+    // Slots loaded whether the wavefront has that many tiles or not.  Tiles are multiplied in pairs, so a slot that may stay
+    // unwritten (an LDS slot may hold anything, NaN included) must not share a pair with one that is in use: it is the
+    // last of an odd number.
+    constexpr int UNC = SP_TPW % 2 == 1 && SP_TPW > 1 ? SP_TPW - 1 : SP_TPW;
+    constexpr int SP_MAXT = SP_WAVES * SP_TPW;  // tiles per pass
     constexpr int KS = D / 32;                  // MFMA k-steps of the score product
     constexpr int DV = D / DS;                  // V channels (and output channels) of this workgroup
     constexpr int DT = DV / 16;                 // 16-channel tiles of O^T
@@ -102,9 +107,8 @@ __global__ __launch_bounds__(SP_WAVES * 64) __attribute__((amdgpu_waves_per_eu(2
     // V tiles: slot j*8 + wave belongs to this wavefront alone (distinct compile-time offsets, so
     // the compiler sees that the direct loads never overlap).  After the key loop the same memory
     // holds the eight partial results and their (max, sum) pairs.
-    __shared__ __attribute__((aligned(1024))) unsigned char vlds[SP_MAXT * TILE_BYTES];
-    constexpr int PART_BYTES = SP_WAVES * DT * 64 * 16;
-    static_assert(PART_BYTES + 2 * SP_WAVES * 16 * 4 <= SP_MAXT * TILE_BYTES, "merge buffers must fit in the V tiles");
+    constexpr int PART_BYTES = SP_WAVES * DT * 64 * 16, MERGE_BYTES = PART_BYTES + 2 * SP_WAVES * 16 * 4;
+    __shared__ __attribute__((aligned(1024))) unsigned char vlds[SP_MAXT * TILE_BYTES > MERGE_BYTES ? SP_MAXT * TILE_BYTES : MERGE_BYTES];
     float (*ml)[SP_WAVES][16] = reinterpret_cast<float (*)[SP_WAVES][16]>(vlds + PART_BYTES);
 
     const int h = wg_x(), rt = wg_y() / DS, dpart = wg_y() % DS;
@@ -234,17 +238,19 @@ __global__ __launch_bounds__(SP_WAVES * 64) __attribute__((amdgpu_waves_per_eu(2
                                                  (__attribute__((address_space(3))) void *)(dst + n * 1024), 16, 0, 0);
             }
         };
-        // the first SP_TPW-1 tile slots unconditionally; the last slot is filled for few wavefronts
+        // the first UNC tile slots unconditionally; a last slot beyond them is filled for few wavefronts
         // only, so it sits behind a branch (nothing right after the branches depends on a pending load)
         // (all K before any V, so that the scores can start while V is still arriving)
 #pragma unroll
-        for (int j = 0; j < SP_TPW - 1; ++j) load_k(j);
+        for (int j = 0; j < UNC; ++j) load_k(j);
+        if constexpr (UNC < SP_TPW) {
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) kraw[SP_TPW - 1][ks] = u32x4_t{0u, 0u, 0u, 0u};
-        if (my_tiles == SP_TPW) load_k(SP_TPW - 1);
+            for (int ks = 0; ks < KS; ++ks) kraw[SP_TPW - 1][ks] = u32x4_t{0u, 0u, 0u, 0u};
+            if (my_tiles == SP_TPW) load_k(SP_TPW - 1);
+        }
 #pragma unroll
-        for (int j = 0; j < SP_TPW - 1; ++j) load_v(j);
-        if (my_tiles == SP_TPW) load_v(SP_TPW - 1);
+        for (int j = 0; j < UNC; ++j) load_v(j);
+        if (UNC < SP_TPW && my_tiles == SP_TPW) load_v(SP_TPW - 1);
 
         __builtin_amdgcn_sched_barrier(0);     // keep every load ahead of the first MFMA (and its wait)
         // K tile j has landed when at most this many younger loads are outstanding.  The counts assume
@@ -254,10 +260,10 @@ __global__ __launch_bounds__(SP_WAVES * 64) __attribute__((amdgpu_waves_per_eu(2
             const int from = 4 * (4 * l16 + lg4);            // byte address of the source lane for ds_bpermute
             static_for<SP_TPW>([&](auto J) {
                 constexpr int j = decltype(J)::value;
-                constexpr int younger = (j < SP_TPW - 1 ? (SP_TPW - 2 - j) * KS : 0) + (SP_TPW - 1) * VLOADS;
+                constexpr int younger = (j < UNC ? (UNC - 1 - j) * KS : 0) + UNC * VLOADS;
                 static_for<KS>([&](auto S) {
                     constexpr int ks = decltype(S)::value;
-                    vm_wait<younger + (j < SP_TPW - 1 ? KS - 1 - ks : 0)>(kraw[j][ks]);
+                    vm_wait<younger + (j < UNC ? KS - 1 - ks : 0)>(kraw[j][ks]);
                     if constexpr (j == 0 && ks == 0)      // the queries are older than this K piece: landed, and not to be touched before here
                         hold_regs(qraw);
                     u32x4_t t;
@@ -353,7 +359,7 @@ __global__ __launch_bounds__(SP_WAVES * 64) __attribute__((amdgpu_waves_per_eu(2
             }
           });
         };
-        pv(std::integral_constant<int, SP_TPW - 1>{});       // counts without the conditional last slot: never too lax
+        pv(std::integral_constant<int, UNC>{});       // counts without the conditional last slot: never too lax
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");    // slots past this wavefront's last tile were loaded too
     };
     run_pass(0);
@@ -428,13 +434,28 @@ hipError_t launch_compact(const void *k_src, const void *v_src, const int32_t *i
     return hipGetLastError();
 }
 
-template <int D, int DS>
-static hipError_t launch_sparse(const SparseArgs &a, bool compact, hipStream_t stream)
+template <int D, int DS, int TPW>
+static hipError_t launch_sparse(SparseArgs a, bool compact, hipStream_t stream)
 {
+    a.npass = (a.ntiles + SP_WAVES * TPW - 1) / (SP_WAVES * TPW);
+    a.tpp = (a.ntiles + a.npass - 1) / a.npass;
     dim3 grid(a.Hkv, ((a.R + 15) / 16) * DS), block(SP_WAVES * 64);
-    if (compact) hipLaunchKernelGGL((sparse_bf16_kernel<D, DS, true>), grid, block, 0, stream, a);
-    else hipLaunchKernelGGL((sparse_bf16_kernel<D, DS, false>), grid, block, 0, stream, a);
+    if (compact) hipLaunchKernelGGL((sparse_bf16_kernel<D, DS, TPW, true>), grid, block, 0, stream, a);
+    else hipLaunchKernelGGL((sparse_bf16_kernel<D, DS, TPW, false>), grid, block, 0, stream, a);
     return hipGetLastError();
+}
+
+// One, two, three or five tiles per wavefront, whichever first holds all keys in one pass (five, and more passes, otherwise):
+// what a wavefront requests without having it, it pays for in cold code and in traffic (28 heads in 4 groups, B = 8: k = 64
+// 4.9 us with five, 3.4 with one; k = 200 5.6 us with five, 4.3 with two; k = 300 5.6 and 4.7 with three).  Nine instead of two
+// passes of five are hardly faster (k = 1000: 8.8 against 9.0 us).
+template <int D, int DS>
+static hipError_t launch_sparse_any(const SparseArgs &a, bool compact, hipStream_t stream)
+{
+    if (a.ntiles <= SP_WAVES) return launch_sparse<D, DS, 1>(a, compact, stream);
+    if (a.ntiles <= 2 * SP_WAVES) return launch_sparse<D, DS, 2>(a, compact, stream);
+    if (a.ntiles <= 3 * SP_WAVES) return launch_sparse<D, DS, 3>(a, compact, stream);
+    return launch_sparse<D, DS, 5>(a, compact, stream);
 }
 
 // The output channels are split over as many workgroups (1, 2 or 4 per row tile) as still leaves
@@ -450,20 +471,18 @@ hipError_t bf16_sparse(const KernelArgs &k, int d, bool compact, hipStream_t str
     a.B = k.B; a.Hq = k.Hq; a.Hkv = k.Hkv; a.G = k.G; a.R = k.R;
     a.nc = (int)k.nc; a.n_blk = k.n_blk;
     a.ntiles = (a.nc + a.n_blk + SP_KT - 1) / SP_KT;
-    a.npass = (a.ntiles + SP_MAXT - 1) / SP_MAXT;
-    a.tpp = (a.ntiles + a.npass - 1) / a.npass;
     a.inv_B = k.B >= 2 ? (unsigned)(((1ull << 32) + k.B - 1) / k.B) : 0u;
     a.scale_log2 = k.scale_log2;
     const long long wgs = (long long)a.Hkv * ((a.R + 15) / 16);
     const int ds = 4 * wgs <= kBf16Workgroups ? 4 : 2 * wgs <= kBf16Workgroups ? 2 : 1;
     if (d == 128) {
-        if (ds == 4) return launch_sparse<128, 4>(a, compact, stream);
-        if (ds == 2) return launch_sparse<128, 2>(a, compact, stream);
-        return launch_sparse<128, 1>(a, compact, stream);
+        if (ds == 4) return launch_sparse_any<128, 4>(a, compact, stream);
+        if (ds == 2) return launch_sparse_any<128, 2>(a, compact, stream);
+        return launch_sparse_any<128, 1>(a, compact, stream);
     }
     if (d == 64) {
-        if (ds >= 2) return launch_sparse<64, 2>(a, compact, stream);
-        return launch_sparse<64, 1>(a, compact, stream);
+        if (ds >= 2) return launch_sparse_any<64, 2>(a, compact, stream);
+        return launch_sparse_any<64, 1>(a, compact, stream);
     }
     return hipErrorInvalidValue;
 }
