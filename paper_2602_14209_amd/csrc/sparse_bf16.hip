@@ -3,7 +3,7 @@
 //
 // The step moves a few MB, so it is bound by dependent-load latency and by how many compute
 // units take part, not by bandwidth.  Layout of the work, chosen for that:
-//   - one workgroup per (KV head, 16 query rows, slice of the output channels); its 8 wavefronts
+//   - one workgroup per (KV head, 16 query rows, slice of the output channels); its 8 (or 16) wavefronts
 //     split the KEYS (tiles of 16 key positions, round-robin), so no partial result ever leaves
 //     the compute unit: the eight partial (max, sum, O) are merged through LDS and every output
 //     element is written once;
@@ -44,7 +44,6 @@ typedef short s16x4_t __attribute__((ext_vector_type(4)));
 typedef short s16x8_t __attribute__((ext_vector_type(8)));
 typedef unsigned short u16;
 
-constexpr int SP_WAVES = 8;
 constexpr int SP_KT = 16;          // key positions per tile
 
 // The compiler may not read, copy or move these registers across this point (they are the
@@ -86,8 +85,8 @@ struct SparseArgs {
 // full scores (every K row, all D channels) but fetches and multiplies only its D/DS channels of
 // V: no result crosses workgroups, the softmax statistics are simply computed DS times, and a
 // compute unit has 1/DS of the V bytes to pull through its memory path.
-template <int D, int DS, int SP_TPW, bool COMPACT>
-__global__ __launch_bounds__(SP_WAVES * 64) __attribute__((amdgpu_waves_per_eu(2))) void sparse_bf16_kernel(const SparseArgs a)
+template <int D, int DS, int SP_TPW, int SP_WAVES, bool COMPACT>
+__global__ __launch_bounds__(SP_WAVES * 64) __attribute__((amdgpu_waves_per_eu(SP_WAVES / 4))) void sparse_bf16_kernel(const SparseArgs a)
 {
     // Slots loaded whether the wavefront has that many tiles or not.  Tiles are multiplied in pairs, so a slot that may stay
     // unwritten (an LDS slot may hold anything, NaN included) must not share a pair with one that is in use: it is the
@@ -434,24 +433,32 @@ hipError_t launch_compact(const void *k_src, const void *v_src, const int32_t *i
     return hipGetLastError();
 }
 
-template <int D, int DS, int TPW>
+template <int D, int DS, int TPW, int SP_WAVES = 8>
 static hipError_t launch_sparse(SparseArgs a, bool compact, hipStream_t stream)
 {
     a.npass = (a.ntiles + SP_WAVES * TPW - 1) / (SP_WAVES * TPW);
     a.tpp = (a.ntiles + a.npass - 1) / a.npass;
     dim3 grid(a.Hkv, ((a.R + 15) / 16) * DS), block(SP_WAVES * 64);
-    if (compact) hipLaunchKernelGGL((sparse_bf16_kernel<D, DS, TPW, true>), grid, block, 0, stream, a);
-    else hipLaunchKernelGGL((sparse_bf16_kernel<D, DS, TPW, false>), grid, block, 0, stream, a);
+    if (compact) hipLaunchKernelGGL((sparse_bf16_kernel<D, DS, TPW, SP_WAVES, true>), grid, block, 0, stream, a);
+    else hipLaunchKernelGGL((sparse_bf16_kernel<D, DS, TPW, SP_WAVES, false>), grid, block, 0, stream, a);
     return hipGetLastError();
 }
 
 // One, two, three or five tiles per wavefront, whichever first holds all keys in one pass (five, and more passes, otherwise):
 // what a wavefront requests without having it, it pays for in cold code and in traffic (28 heads in 4 groups, B = 8: k = 64
-// 4.9 us with five, 3.4 with one; k = 200 5.6 us with five, 4.3 with two; k = 300 5.6 and 4.7 with three).  Nine instead of two
-// passes of five are hardly faster (k = 1000: 8.8 against 9.0 us).
+// 4.9 us with five, 3.6 with one; k = 200 5.6 us with five, 4.2 with two; k = 300 5.6 and 4.7 with three).  Where sixteen
+// wavefronts save a pass, they are taken (registers: three tiles each at d = 128, five at d = 64; LDS: channels split to 32):
+// k = 700 8.6 us in two passes of eight, 7.0 in one of sixteen; where they do not, eight are faster (k = 1000: 8.6 against
+// 9.7 us).  Nine tiles per wavefront instead of two passes of five are hardly faster (k = 1000: 8.8 against 9.0 us).
 template <int D, int DS>
 static hipError_t launch_sparse_any(const SparseArgs &a, bool compact, hipStream_t stream)
 {
+    constexpr int SP_WAVES = 8;
+    if constexpr (D / DS <= 32) {
+        if ((a.ntiles > 40 && a.ntiles <= 48) || (a.ntiles > 80 && a.ntiles <= 96)) return launch_sparse<D, DS, 3, 16>(a, compact, stream);
+        if constexpr (D == 64)
+            if (a.ntiles > 48 && a.ntiles <= 80) return launch_sparse<D, DS, 5, 16>(a, compact, stream);
+    }
     if (a.ntiles <= SP_WAVES) return launch_sparse<D, DS, 1>(a, compact, stream);
     if (a.ntiles <= 2 * SP_WAVES) return launch_sparse<D, DS, 2>(a, compact, stream);
     if (a.ntiles <= 3 * SP_WAVES) return launch_sparse<D, DS, 3>(a, compact, stream);
