@@ -335,7 +335,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void c
 
 hipError_t f32_attn(const KernelArgs &a, int d, int row_groups, bool gather, hipStream_t stream)
 {
-    if (a.rw != 1 && a.rw != 2 && a.rw != 4) return hipErrorInvalidValue;
+    if (a.rw != 1 && a.rw != 2) return hipErrorInvalidValue;
     dim3 grid(a.Hkv, a.n_split, row_groups), block(kF32Waves * 64);
     if (d == 128) {
         if (gather) hipLaunchKernelGGL((attn_f32_kernel<128, F32_ATTN, true>), grid, block, 0, stream, a);
@@ -351,7 +351,7 @@ hipError_t f32_attn(const KernelArgs &a, int d, int row_groups, bool gather, hip
 
 hipError_t f32_stats(const KernelArgs &a, int d, int row_groups, hipStream_t stream)
 {
-    if (a.rw != 1 && a.rw != 2 && a.rw != 4) return hipErrorInvalidValue;
+    if (a.rw != 1 && a.rw != 2) return hipErrorInvalidValue;
     dim3 grid(a.Hkv, a.n_split, row_groups), block(kF32Waves * 64);
     if (d == 128) hipLaunchKernelGGL((attn_f32_kernel<128, F32_STATS, false>), grid, block, 0, stream, a);
     else if (d == 64) hipLaunchKernelGGL((attn_f32_kernel<64, F32_STATS, false>), grid, block, 0, stream, a);

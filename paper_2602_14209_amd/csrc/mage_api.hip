@@ -181,7 +181,7 @@ int run_sparse_bf16(const mage_shape *shape, bool compact, int n_seq, const void
         !aligned16(out))
         return MAGE_ERR_ALIGN;
     SplitPlan p{};
-    plan_rows(*shape, p);
+    plan_rows(*shape, p, shape->k);
     p.n_split = 1;
     p.n_cyc = 1;
     KernelArgs a = base_args(*shape, p);

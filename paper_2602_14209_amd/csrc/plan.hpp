@@ -25,7 +25,7 @@ struct SplitPlan {
     int rpad;         // row_groups * rows_per_wg
     int waves;        // wavefronts per workgroup of the column-sum pass (one per 32 rows; MFMA path)
     int tile;         // keys per tile (fp32: keys a workgroup covers per round, 16 per key slice)
-    int rw;           // fp32: 16-row tiles per workgroup; its 8 wavefronts are rw row tiles x 8/rw key slices
+    int rw;           // fp32: 16-row tiles per workgroup (1 or 2); its 8 wavefronts are rw row tiles x 8/rw key slices
     int kps;          // cache keys per split (multiple of tile)
     int n_split;      // splits along the key axis, including a block-only split if any
     int n_cyc;        // splits that own cache keys (the first n_cyc)
@@ -35,7 +35,15 @@ struct SplitPlan {
 inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 inline int ceil_div(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
 
-inline void plan_rows(const mage_shape &s, SplitPlan &p)
+// 16-key tiles of the fp32 kernels: those of the cache, then those of the block, which no tile mixes
+inline int64_t f32_key_tiles(int64_t cache_keys, int block_keys) { return (cache_keys + 15) / 16 + (block_keys + 15) / 16; }
+
+// `keys`: cache keys of the pass.  fp32: a workgroup with two row tiles reads its keys once for both; four would leave two key
+// slices, twice the splits for the same number of workgroups and twice the partial results (B*G = 64, L = 16384, d = 128: 34.6 against
+// 33.4 us; 224 rows: 95.6 against 86.4, 14 row tiles being no multiple of four).  One row tile and eight key slices while all
+// of that fits the chip in one round, where only the length of the round counts (k = 200, B*G = 64: 12.3 us; 17.3 with two
+// row tiles, 20.9 with four).
+inline void plan_rows(const mage_shape &s, SplitPlan &p, int64_t keys)
 {
     p.R = (s.Hq / s.Hkv) * s.B;
     if (s.dtype == MAGE_BF16) {
@@ -43,9 +51,9 @@ inline void plan_rows(const mage_shape &s, SplitPlan &p)
         p.waves = p.R > 128 ? 8 : 4;
         p.tile = kBf16Tile;
     } else {
-        // as many row tiles as there are, up to four: they read the same keys; the other wavefronts split the keys
         p.waves = 4;
-        p.rw = p.R > 32 ? 4 : p.R > 16 ? 2 : 1;
+        const int64_t one_round = (int64_t)s.Hkv * ceil_div(p.R, 16) * ((keys + 127) / 128);
+        p.rw = p.R > 16 && one_round > kF32Workgroups ? 2 : 1;
         p.rows_per_wg = 16 * p.rw;
         p.tile = 16 * (8 / p.rw);
     }
@@ -57,17 +65,19 @@ inline void plan_rows(const mage_shape &s, SplitPlan &p)
 // others ends that much later, so the count stays at or below a multiple of 256: with tiles of 64 keys, 33 splits of 8 heads (264
 // workgroups of 2 tiles) measured 16.5 us where 22 splits (176 of 3 tiles) take 12.9.  Every workgroup pays a fixed 4 to
 // 5 us (cold code, first tile, merge), so up to 64 tiles go one per split (L = 1500, B = 8, 16 heads: 11.0 us against 13.2
-// with at least four); beyond that a split has at least two, because exact attention pays a [rows x d] partial per split.
+// with at least four); beyond that a split has at least two, because exact attention pays a [rows x d] partial per split.  The
+// fp32 kernels pay 1.9 us (d = 128) per round of tiles, more than a partial costs (B*G = 16, L = 1024: 12.9 us with one round,
+// 16.0 with two, 21.4 with four).
 inline SplitPlan plan_dense(const mage_shape &s, int target_workgroups = 0, bool rows_in_one_workgroup = false)
 {
     SplitPlan p{};
-    plan_rows(s, p);
+    plan_rows(s, p, s.L);
     if (target_workgroups == 0) target_workgroups = s.dtype == MAGE_BF16 ? kBf16Workgroups : kF32Workgroups;
     const int64_t tiles = (s.L + p.tile - 1) / p.tile;
     const int64_t per_split = (int64_t)s.Hkv * (rows_in_one_workgroup ? 1 : p.row_groups);   // workgroups per key split
     const int64_t target = target_workgroups / per_split > 0 ? target_workgroups / per_split : 1;
     int64_t tps = (tiles + target - 1) / target;     // tiles per split
-    const int64_t min_tps = s.dtype == MAGE_BF16 ? (tiles <= 64 ? 1 : 2) : 4;
+    const int64_t min_tps = s.dtype == MAGE_BF16 && tiles > 64 ? 2 : 1;
     if (tps < min_tps) tps = min_tps;
     p.n_split = (int)((tiles + tps - 1) / tps);
     p.kps = (int)(tps * p.tile);
@@ -98,7 +108,7 @@ inline SplitPlan plan_colsum(const mage_shape &s)
     if (s.dtype != MAGE_BF16) {
         // a workgroup's four wavefronts take 32 keys each per round
         SplitPlan p{};
-        plan_rows(s, p);
+        plan_rows(s, p, s.L);
         p.tile = 128;
         const int64_t tiles = (s.L + p.tile - 1) / p.tile;
         const int64_t target = kF32ColsumWorkgroups / s.Hkv > 0 ? kF32ColsumWorkgroups / s.Hkv : 1;
@@ -120,17 +130,19 @@ inline SplitPlan plan_colsum(const mage_shape &s)
 constexpr int kMergeSplits = 128, kMergeRows = 256;
 inline bool colsum_merges_stats(int rows, int n_split) { return rows <= kMergeRows && n_split <= kMergeSplits; }
 
-// Sparse step of the fp32 path: k gathered cache keys and the block's own.  Few keys stay in one split (one launch, the
-// key slices of a workgroup are merged on chip); beyond four rounds per workgroup the keys are split to fill the chip.
+// Sparse step: k gathered cache keys and the block's own.  The bf16 kernels merge on chip (one split).  fp32: a second launch
+// costs what two rounds of tiles cost at d = 128 and three at d = 64 (k = 200, one row tile: 12.1 us either way; 7.7 against
+// 9.6); up to that many stay in one split, whose key slices are merged on chip.
 inline SplitPlan plan_sparse(const mage_shape &s)
 {
     SplitPlan p{};
-    plan_rows(s, p);
-    const int64_t tiles = ((int64_t)s.k + s.B + p.tile - 1) / p.tile;
+    plan_rows(s, p, s.k);
+    const bool f32 = s.dtype != MAGE_BF16;
+    const int64_t slices = p.tile / 16;
+    const int64_t tiles = (f32_key_tiles(s.k, s.B) + slices - 1) / slices;
     const int64_t per_split = (int64_t)s.Hkv * p.row_groups;
     const int64_t target = kF32Workgroups / per_split > 0 ? kF32Workgroups / per_split : 1;
-    int64_t tps = (tiles + target - 1) / target;
-    if (tps < 4) tps = 4;
+    const int64_t tps = !f32 || tiles <= (s.d == 64 ? 3 : 2) ? tiles : (tiles + target - 1) / target;
     p.n_split = (int)((tiles + tps - 1) / tps);
     p.kps = (int)(tps * p.tile);
     p.n_cyc = p.n_split;

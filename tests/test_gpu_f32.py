@@ -1,4 +1,4 @@
-"""fp32 kernels at the edges of their tiling: 16-row tiles (one, two or four per workgroup), 16-key tiles dealt to key
+"""fp32 kernels at the edges of their tiling: 16-row tiles (one or two per workgroup), 16-key tiles dealt to key
 slices and splits, 32-key units of the column sums; gathered, dense and fused entry points against the oracle."""
 import zlib
 
@@ -15,10 +15,12 @@ pytestmark = pytest.mark.gpu
     ("e1", 1, 1, 64, 1, 1, 1),               # one row, one key
     ("e2", 4, 1, 64, 15, 4, 15),             # 16 rows, a ragged first tile, fewer tiles than key slices
     ("e3", 17, 1, 128, 17, 1, 3),            # 17 rows: two row tiles
-    ("e4", 6, 2, 128, 129, 11, 128),         # 33 rows: four row tiles, the last one empty
-    ("e5", 5, 1, 64, 2049, 13, 700),         # 65 rows: two row groups; gathered keys in several splits
+    ("e4", 6, 2, 128, 129, 11, 128),         # 33 rows: three row tiles
+    ("e5", 5, 1, 64, 2049, 13, 700),         # 65 rows: five row tiles; gathered keys in several splits
     ("e6", 8, 4, 128, 3001, 16, 531),        # several splits everywhere
     ("e7", 2, 2, 64, 33, 7, 16),             # block tiles only in some slices
+    ("e8", 24, 8, 64, 1400, 11, 700),        # 33 rows and more than one round of workgroups: two row tiles each, the last one empty
+    ("e9", 4, 1, 64, 1000, 4, 380),          # gathered: one round per split, the last split with the block tile only
 ])
 def test_f32_edges(oracle_mod, case):
     from gpu_util import Problem, check_alpha, check_index_sets, check_out
