@@ -447,15 +447,17 @@ static hipError_t launch_sparse(SparseArgs a, bool compact, hipStream_t stream)
 // One, two, three or five tiles per wavefront, whichever first holds all keys in one pass (five, and more passes, otherwise):
 // what a wavefront requests without having it, it pays for in cold code and in traffic (28 heads in 4 groups, B = 8: k = 64
 // 4.9 us with five, 3.6 with one; k = 200 5.6 us with five, 4.2 with two; k = 300 5.6 and 4.7 with three).  Where sixteen
-// wavefronts save a pass, they are taken (registers: three tiles each at d = 128, five at d = 64; LDS: channels split to 32):
-// k = 700 8.6 us in two passes of eight, 7.0 in one of sixteen; where they do not, eight are faster (k = 1000: 8.6 against
-// 9.7 us).  Nine tiles per wavefront instead of two passes of five are hardly faster (k = 1000: 8.8 against 9.0 us).
+// wavefronts save a pass, they are taken (registers: four tiles each at d = 128, five at d = 64; LDS: channels split to 32):
+// k = 700 8.6 us in two passes of eight, 7.0 in one of sixteen with three tiles each, k = 900 8.6 and 7.9 with four; where they
+// do not, eight are faster (k = 1000: 8.6 against 9.7 us in two passes of sixteen with three).  Nine tiles per wavefront instead of two passes of five are hardly faster (k = 1000: 8.8 against 9.0 us).
 template <int D, int DS>
 static hipError_t launch_sparse_any(const SparseArgs &a, bool compact, hipStream_t stream)
 {
     constexpr int SP_WAVES = 8;
     if constexpr (D / DS <= 32) {
         if ((a.ntiles > 40 && a.ntiles <= 48) || (a.ntiles > 80 && a.ntiles <= 96)) return launch_sparse<D, DS, 3, 16>(a, compact, stream);
+        if constexpr (D == 128)
+            if (a.ntiles > 48 && a.ntiles <= 64) return launch_sparse<D, DS, 4, 16>(a, compact, stream);
         if constexpr (D == 64)
             if (a.ntiles > 48 && a.ntiles <= 80) return launch_sparse<D, DS, 5, 16>(a, compact, stream);
     }

@@ -9,7 +9,7 @@ from paper_2602_14209_amd.workloads import Workload, make_layer
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("keys", [128, 129, 256, 257, 384, 385, 640, 641, 768, 769, 1280, 1281, 1536, 1537])
+@pytest.mark.parametrize("keys", [128, 129, 256, 257, 384, 385, 640, 641, 768, 769, 1024, 1025, 1280, 1281, 1536, 1537])
 @pytest.mark.parametrize("Hq, Hkv, d, B", [(14, 2, 128, 8), (8, 2, 64, 16), (40, 20, 128, 56)])      # channels in four, two parts, unsplit
 def test_key_counts(oracle_mod, keys, Hq, Hkv, d, B):
     from gpu_util import Problem, check_out
