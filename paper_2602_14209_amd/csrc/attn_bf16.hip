@@ -552,7 +552,7 @@ void attn_bf16_kernel(const KernelArgs a)
                 mx = fmaxf(lo, hi) * a.scale_log2;
             }
             if (__any(mx > m_run + kLazy)) {      // uniform: some row's maximum has run ahead of its reference
-                const float m_new = fmaxf(m_run, mx);
+                const float m_new = fmaxf(m_run, ceilf(mx));        // whole numbers: the split merges scale by exact powers of two
                 const float corr = __builtin_amdgcn_exp2f(m_run - m_new);
                 m_run = m_new;
                 l_run *= corr;

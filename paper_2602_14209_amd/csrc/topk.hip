@@ -219,9 +219,9 @@ __device__ __forceinline__ double exp2_f64(double x)
     return __builtin_amdgcn_ldexp(p, (int)n);
 }
 
-// sum of q[e] * k[e] over the values of a 16-byte piece (8 bf16 or 4 fp32), in order; side: 0, or +1 / -1 to take only the
-// positive / negative part of q
-__device__ __forceinline__ double dot_piece(const uint4 &q, const uint4 &k, int esz, int side, double p)
+// sum of q[e] * k[e] over the values of a 16-byte piece (8 bf16 or 4 fp32), in order; the product of two bf16 values is exact in
+// fp32 (underflow below 2^-126 and overflow aside), which saves a conversion
+__device__ __forceinline__ double dot_piece(const uint4 &q, const uint4 &k, int esz, double p)
 {
     const uint32_t a[4] = {q.x, q.y, q.z, q.w}, b[4] = {k.x, k.y, k.z, k.w};
 #pragma unroll
@@ -230,34 +230,66 @@ __device__ __forceinline__ double dot_piece(const uint4 &q, const uint4 &k, int 
             p = fma((double)__uint_as_float(a[i]), (double)__uint_as_float(b[i]), p);
             continue;
         }
-#pragma unroll
-        for (int half = 0; half < 2; ++half) {
-            float x = __uint_as_float(half ? a[i] & 0xffff0000u : a[i] << 16);
-            const float y = __uint_as_float(half ? b[i] & 0xffff0000u : b[i] << 16);
-            x = side > 0 ? fmaxf(x, 0.f) : side < 0 ? fminf(x, 0.f) : x;
-            p = fma((double)x, (double)y, p);            // (a product in fp32 would be exact too, but for underflow)
-        }
+        p += (double)(__uint_as_float(a[i] << 16) * __uint_as_float(b[i] << 16));
+        p += (double)(__uint_as_float(a[i] & 0xffff0000u) * __uint_as_float(b[i] & 0xffff0000u));
     }
     return p;
+}
+
+// the positive (neg = false) or negative part of the bf16 values of a piece
+__device__ __forceinline__ uint4 signed_part(const uint4 &x, bool neg)
+{
+    auto part = [&](uint32_t v) {
+        const uint32_t m = ((v >> 15) & 0x00010001u) * 0xffffu;                // all ones where the value is negative
+        return neg ? v & m : v & ~m;
+    };
+    return make_uint4(part(x.x), part(x.y), part(x.z), part(x.w));
+}
+
+// x * 2^e for a whole number e <= 0 (far below -1100 too)
+__device__ __forceinline__ double scale_pow2(double x, float e) { return __builtin_amdgcn_ldexp(x, (int)fmaxf(e, -1100.f)); }
+
+// x of lane (l ^ 1) or (l ^ 2): a quad permutation, no trip through the LDS crossbar
+template <int X>
+__device__ __forceinline__ double quad_xor(double x)
+{
+    constexpr int PERM = X == 1 ? 0xb1 : 0x4e;
+    return __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(x), PERM, 0xf, 0xf, true),
+                            __builtin_amdgcn_update_dpp(0, __double2loint(x), PERM, 0xf, 0xf, true));
 }
 
 // alpha[h, j] in fp64 from the inputs (Eq. 5) for n of the listed elements, j = list[slot[c]].y:
 //   1/(G*B) * sum over the R rows of exp2(q_r.k_j * scale - M_r) / L_r,
 // with (M_r, L_r) the row's softmax statistics merged in fp64 over the key splits.  Four threads per
-// row (a quarter of the channels and of the splits each), 256 rows per pass.  Taken by one head in a few hundred, and then
-// as a tail of the whole selection: with element-by-element loads and the library's exp2 it took 42 us, 14 us now (two candidates, 224 rows).  Every thread of the
-// workgroup calls; out[c] receives the results rounded to fp32 (valid after the final barrier).
+// row (a quarter of the channels and of the splits each), 256 rows per pass.  Taken by one head in a few dozen, and then
+// as a tail of the whole selection, bound by the instructions that sixteen wavefronts issue on one CU and by the dependent loads.  So
+// the references of the statistics are whole numbers (the passes that write them see to it) and their merge needs no exponentials;
+// the first query and key pieces are requested before the statistics, every piece after them one step ahead; and the
+// wavefronts' sums of all candidates meet in LDS once, at the end.  Two candidates, 224 rows: 42 us with element-by-element loads and the
+// library's exp2, 14 us with 16-byte loads and an exp2 of its own, 8 us now.  Every thread of the workgroup calls; out[c] receives the results rounded to fp32 (valid after the final barrier).
 __device__ __forceinline__ void rescore_candidates(const RescoreArgs &rs, int h, const uint2 *list, const uint32_t *slot, int n, float *out,
-                                   float *rowM, double *rowL, double *acc, double *red)
+                                   double *acc, double (*red)[TK_WAVES])
 {
     constexpr int ROWS = TK_THREADS / 4;
     const int lane = tid_x() & 63, wave = tid_x() >> 6;
     const int part = tid_x() & 3, rl = tid_x() >> 2;
     const int cpt = rs.d / 4;
+    const int pieces = cpt * rs.esz / 16;                  // 2, 4 or 8
     if (tid_x() < n) acc[tid_x()] = 0.0;
+    auto key = [&](int c) {
+        const long long ko = ((long long)list[slot[c]].y * rs.Hkv + h) * rs.d + part * cpt;
+        return reinterpret_cast<const uint4 *>(static_cast<const char *>(rs.kc) + ko * rs.esz);
+    };
     for (int r0 = 0; r0 < rs.R; r0 += ROWS) {              // uniform trip count (one pass unless R > 256)
         const int r = r0 + rl;
         const bool live = r < rs.R;
+        // split_q: the queries are rows of d / 2 channels, to be taken as [max(q, 0) | min(q, 0)]  (rows past the last read row 0)
+        const int gl = live ? r / rs.B : 0, qi = live ? r - gl * rs.B : 0;
+        const long long qo = ((long long)qi * rs.Hq + (long long)h * rs.G + gl) * (rs.split_q ? rs.d / 2 : rs.d) + (rs.split_q ? (part & 1) : part) * cpt;
+        const uint4 *qp = reinterpret_cast<const uint4 *>(static_cast<const char *>(rs.q) + qo * rs.esz);
+        const uint4 *kp = key(0);
+        uint4 q0 = qp[0], q1 = qp[1], k0 = kp[0], k1 = kp[1];
+
         // this row's statistics, merged over the key splits, eight in flight per thread
         constexpr int SF = 8;
         float M = -3.0e38f;
@@ -274,64 +306,52 @@ __device__ __forceinline__ void rescore_candidates(const RescoreArgs &rs, int h,
             }
 #pragma unroll
             for (int i = 0; i < SF; ++i) top = fmaxf(top, m[i]);
-            Lr *= exp2_f64((double)M - (double)top);
+            Lr = scale_pow2(Lr, M - top);
             M = top;
+#pragma unroll
+            for (int i = 0; i < SF; ++i) Lr += scale_pow2((double)l[i], m[i] - M);
+        }
+        // the four threads of the row: one common reference, then plain sums
+        float top = fmaxf(M, __shfl_xor(M, 1));
+        top = fmaxf(top, __shfl_xor(top, 2));
+        Lr = scale_pow2(Lr, M - top);
+        Lr += quad_xor<1>(Lr);
+        Lr += quad_xor<2>(Lr);
+        M = top;
+        const double inv = live && part == 0 ? 1.0 / Lr : 0.0;
+
+        for (int c = 0; c < n; ++c) {
+            double p = 0.0;
 #pragma unroll 1
-            for (int i = 0; i < SF; ++i) {               // (rolled: the registers rotate)
-                Lr += (double)l[0] * exp2_f64((double)m[0] - (double)M);
-#pragma unroll
-                for (int e = 0; e + 1 < SF; ++e) {
-                    m[e] = m[e + 1];
-                    l[e] = l[e + 1];
+            for (int i = 0; i < pieces; i += 2) {
+                uint4 qa = q0, qb = q1;
+                const uint4 ka = k0, kb = k1;
+                const bool last = i + 2 == pieces;           // then the next candidate's first pieces (after the last one: its own again)
+                if (last && c + 1 < n) kp = key(c + 1);
+                const int e = last ? 0 : i + 2;
+                q0 = qp[e], q1 = qp[e + 1], k0 = kp[e], k1 = kp[e + 1];
+                if (rs.split_q) {
+                    qa = signed_part(qa, part >= 2);
+                    qb = signed_part(qb, part >= 2);
                 }
+                p = dot_piece(qa, ka, rs.esz, p);
+                p = dot_piece(qb, kb, rs.esz, p);
             }
-        }
+            p += quad_xor<1>(p);
+            p += quad_xor<2>(p);
+            double t = exp2_f64(p * (double)rs.scale_log2 - (double)M) * inv;
 #pragma unroll
-        for (int d = 1; d <= 2; d <<= 1) {               // the four threads of the row
-            const float mo = __shfl_xor(M, d);
-            const double lo = __shfl_xor(Lr, d);
-            const float top = fmaxf(M, mo);
-            Lr = Lr * exp2_f64((double)M - (double)top) + lo * exp2_f64((double)mo - (double)top);
-            M = top;
-        }
-        __syncthreads();                                   // the previous pass is done with rowM / rowL
-        if (part == 0) {
-            rowM[rl] = M;
-            rowL[rl] = Lr;
+            for (int d = 32; d >= 4; d >>= 1) t += __shfl_xor(t, d);           // (rows sit four lanes apart)
+            if (lane == 0) red[c][wave] = t;
         }
         __syncthreads();
-        const int gl = live ? r / rs.B : 0, qi = live ? r - gl * rs.B : 0;
-        // split_q: the queries are rows of d / 2 channels, to be taken as [max(q, 0) | min(q, 0)]
-        const long long qo = ((long long)qi * rs.Hq + (long long)h * rs.G + gl) * (rs.split_q ? rs.d / 2 : rs.d) + (rs.split_q ? (part & 1) : part) * cpt;
-        for (int c = 0; c < n; ++c) {
-            const long long j = (long long)list[slot[c]].y;
-            const long long ko = (j * rs.Hkv + h) * rs.d + part * cpt;
-            double p = 0.0;
-            const uint4 *qp = reinterpret_cast<const uint4 *>(static_cast<const char *>(rs.q) + qo * rs.esz);
-            const uint4 *kp = reinterpret_cast<const uint4 *>(static_cast<const char *>(rs.kc) + ko * rs.esz);
-            const int side = !rs.split_q ? 0 : part < 2 ? 1 : -1;
-            const int pieces = cpt * rs.esz / 16;        // 2, 4 or 8
-            for (int i = 0; i < pieces; i += 2) {        // (rows past the last read row 0)
-                const uint4 q0 = qp[i], q1 = qp[i + 1], k0 = kp[i], k1 = kp[i + 1];
-                p = dot_piece(q0, k0, rs.esz, side, p);
-                p = dot_piece(q1, k1, rs.esz, side, p);
-            }
-            p += __shfl_xor(p, 1);
-            p += __shfl_xor(p, 2);
-            double t = (live && part == 0) ? exp2_f64(p * (double)rs.scale_log2 - (double)rowM[rl]) / rowL[rl] : 0.0;
-#pragma unroll
-            for (int d = 32; d >= 1; d >>= 1) t += __shfl_xor(t, d);
-            __syncthreads();                               // red may still be read from the previous candidate
-            if (lane == 0) red[wave] = t;
-            __syncthreads();
-            if (tid_x() == 0) {
-                double tot = 0.0;
-                for (int w = 0; w < TK_WAVES; ++w) tot += red[w];      // fixed order
-                acc[c] += tot;
-            }
+        if (tid_x() < n) {
+            double tot = 0.0;
+            for (int w = 0; w < TK_WAVES; ++w) tot += red[tid_x()][w];      // fixed order
+            acc[tid_x()] += tot;
         }
+        __syncthreads();                                   // the next pass writes red
     }
-    __syncthreads();
     if (tid_x() < n) out[tid_x()] = (float)(acc[tid_x()] * rs.inv_rows);
     __syncthreads();
 }
@@ -408,8 +428,7 @@ __global__ __launch_bounds__(TK_THREADS) void topk_kernel(const float *alpha, co
     __shared__ uint32_t n_hit, n_cand, n_win, n_list, n_near, n_near_in, thr_bits, next_bits;
     __shared__ uint32_t near_slot[TK_NEAR_MAX];          // list entries within eps of the k-th value
     __shared__ float near_val[TK_NEAR_MAX];              // their fp64 score, rounded to fp32
-    __shared__ double red64[TK_WAVES], near_acc[TK_NEAR_MAX], rowL[TK_THREADS / 4];
-    __shared__ float rowM[TK_THREADS / 4];
+    __shared__ double near_red[TK_NEAR_MAX][TK_WAVES], near_acc[TK_NEAR_MAX];
 
     const int h = wg_x();
     const uint32_t *u = reinterpret_cast<const uint32_t *>(alpha) + (long long)h * L;
@@ -664,7 +683,7 @@ __global__ __launch_bounds__(TK_THREADS) void topk_kernel(const float *alpha, co
                 __syncthreads();
                 const uint32_t nn = n_near, nin = n_near_in;
                 if (nn <= TK_NEAR_MAX) {                 // more of them (massive ties) keep the fp32 ranking
-                    rescore_candidates(rs, h, list, near_slot, (int)nn, near_val, rowM, rowL, near_acc, red64);
+                    rescore_candidates(rs, h, list, near_slot, (int)nn, near_val, near_acc, near_red);
                     if (t < (int)nn) {                   // rank among the near elements: value, then smaller position
                         const uint32_t me = near_slot[t], j = list[me].y;
                         const float v = near_val[t];
