@@ -76,22 +76,28 @@ struct SparseArgs {
     int ntiles, npass, tpp;      // tiles of SP_KT key positions, passes over the LDS window, tiles per pass (balanced)
     unsigned inv_B;              // ceil(2^32 / B) for B >= 2: row / B == mulhi(row, inv_B) while row * B < 2^32
     float scale_log2;
+    unsigned inv_Hkv;            // SP_SEQS: the same for unit / Hkv
+    long long seq_q, seq_kv, seq_idx, seq_blk, seq_out, seq_lse;      // SP_SEQS: element strides between sequences
 };
 
-// COMPACT: the k cache positions are rows 0..k-1 of a compacted cache (no index set to read).
+// Where the k cache positions come from: gathered by the index set; rows 0..k-1 of a compacted cache (no index set to
+// read); gathered, x of the grid = (sequence, KV head)
+enum { SP_GATHER = 0, SP_COMPACT = 1, SP_SEQS = 2 };
+
 // SP_TPW: tiles per wavefront and pass (register arrays; nearly all are loaded whether the wavefront has that many or
 // not, so a call takes the smallest that holds its keys in one pass).
 // DS: the output channels of a row tile are dealt to DS workgroups.  Each of them computes the
 // full scores (every K row, all D channels) but fetches and multiplies only its D/DS channels of
 // V: no result crosses workgroups, the softmax statistics are simply computed DS times, and a
 // compute unit has 1/DS of the V bytes to pull through its memory path.
-template <int D, int DS, int SP_TPW, int SP_WAVES, bool COMPACT>
+template <int D, int DS, int SP_TPW, int SP_WAVES, int SOURCE>
 __global__ __launch_bounds__(SP_WAVES * 64) __attribute__((amdgpu_waves_per_eu(SP_WAVES / 4))) void sparse_bf16_kernel(const SparseArgs a)
 {
     // Slots loaded whether the wavefront has that many tiles or not.  Tiles are multiplied in pairs, so a slot that may stay
     // unwritten (an LDS slot may hold anything, NaN included) must not share a pair with one that is in use: it is the
     // last of an odd number.
     constexpr int UNC = SP_TPW % 2 == 1 && SP_TPW > 1 ? SP_TPW - 1 : SP_TPW;
+    constexpr bool COMPACT = SOURCE == SP_COMPACT;
     constexpr int SP_MAXT = SP_WAVES * SP_TPW;  // tiles per pass
     constexpr int KS = D / 32;                  // MFMA k-steps of the score product
     constexpr int DV = D / DS;                  // V channels (and output channels) of this workgroup
@@ -110,7 +116,7 @@ __global__ __launch_bounds__(SP_WAVES * 64) __attribute__((amdgpu_waves_per_eu(S
     __shared__ __attribute__((aligned(1024))) unsigned char vlds[SP_MAXT * TILE_BYTES > MERGE_BYTES ? SP_MAXT * TILE_BYTES : MERGE_BYTES];
     float (*ml)[SP_WAVES][16] = reinterpret_cast<float (*)[SP_WAVES][16]>(vlds + PART_BYTES);
 
-    const int h = wg_x(), rt = wg_y() / DS, dpart = wg_y() % DS;
+    const int unit = wg_x(), rt = wg_y() / DS, dpart = wg_y() % DS;
     const int lane = tid_x() & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid_x() >> 6);     // uniform: tile bookkeeping stays on the scalar unit
     const int l16 = lane & 15, lg4 = lane >> 4;
@@ -119,7 +125,9 @@ __global__ __launch_bounds__(SP_WAVES * 64) __attribute__((amdgpu_waves_per_eu(S
     const int n_keys = a.nc + a.n_blk;
     const int ntiles = a.ntiles, npass = a.npass, tpp = a.tpp;
 
-    const int32_t *idx = COMPACT ? nullptr : a.idx + (long long)h * a.nc;
+    const int sq = SOURCE != SP_SEQS ? 0 : a.Hkv == 1 ? unit : (int)(((unsigned long long)(unsigned)unit * a.inv_Hkv) >> 32), h = unit - sq * a.Hkv;
+    const long long seq = sq;
+    const int32_t *idx = COMPACT ? nullptr : a.idx + seq * a.seq_idx + (long long)h * a.nc;
 
     // row of q, out and lse that this lane's query row is (rows past R stand in for the last row and are never stored)
     auto io_row = [&]() {
@@ -185,15 +193,15 @@ __global__ __launch_bounds__(SP_WAVES * 64) __attribute__((amdgpu_waves_per_eu(S
                                                // longest dependent chain of the launch (entry -> row -> scores), and the code
                                                // in front of them is fetched from a cold instruction cache
         const unsigned stride_bytes = (unsigned)a.Hkv * (D * 2);       // bytes from a cache row to the next
-        const u16 *kc = static_cast<const u16 *>(a.kc) + h * D;
-        const u16 *vc = static_cast<const u16 *>(a.vc) + h * D + dpart * DV;
-        const u16 *kb = static_cast<const u16 *>(a.kblk) + h * D;
-        const u16 *vb = static_cast<const u16 *>(a.vblk) + h * D + dpart * DV;
+        const u16 *kc = static_cast<const u16 *>(a.kc) + seq * a.seq_kv + h * D;
+        const u16 *vc = static_cast<const u16 *>(a.vc) + seq * a.seq_kv + h * D + dpart * DV;
+        const u16 *kb = static_cast<const u16 *>(a.kblk) + seq * a.seq_blk + h * D;
+        const u16 *vb = static_cast<const u16 *>(a.vblk) + seq * a.seq_blk + h * D + dpart * DV;
         if (pass == 0) {
             // The queries: assembly loads like the K rows (the compiler must not count them: its wait for them would
             // sit in front of the first MFMA and take most of the K and V loads with it).  They are older than every
             // K row, so they have landed when the first K tile has.
-            const u16 *src = static_cast<const u16 *>(a.q) + (long long)io_row() * D + 8 * lg4;
+            const u16 *src = static_cast<const u16 *>(a.q) + seq * a.seq_q + (long long)io_row() * D + 8 * lg4;
             static_for<KS>([&](auto S) {
                 constexpr int ks = decltype(S)::value;
                 qraw[ks] = global_load_b128<ks * 64>(src);
@@ -388,7 +396,7 @@ __global__ __launch_bounds__(SP_WAVES * 64) __attribute__((amdgpu_waves_per_eu(S
     }
     if (row >= a.R) return;
     const int orow = io_row();
-    float *out = a.out;
+    float *out = a.out + seq * a.seq_out;
     const float inv = 1.f / lt;
     for (int dt = wave; dt < DT; dt += SP_WAVES) {
         f32x4_t acc = f32x4_t{0.f, 0.f, 0.f, 0.f};
@@ -396,7 +404,7 @@ __global__ __launch_bounds__(SP_WAVES * 64) __attribute__((amdgpu_waves_per_eu(S
         for (int w = 0; w < SP_WAVES; ++w) acc += part[(w * DT + dt) * 64 + lane] * wgt[w];
         *reinterpret_cast<f32x4_t *>(out + (long long)orow * D + dpart * DV + 16 * dt + 4 * lg4) = acc * inv;
     }
-    if (a.lse_out && dpart == 0 && wave == 0 && lg4 == 0) a.lse_out[orow] = (M + log2f(lt)) * 0.6931471805599453f;
+    if (a.lse_out && dpart == 0 && wave == 0 && lg4 == 0) a.lse_out[seq * a.seq_lse + orow] = (M + log2f(lt)) * 0.6931471805599453f;
 }
 
 // Copies the selected rows into a cache of length k: dst[p,h,:] = src[idx[h,p],h,:] (16 bytes per
@@ -434,13 +442,14 @@ hipError_t launch_compact(const void *k_src, const void *v_src, const int32_t *i
 }
 
 template <int D, int DS, int TPW, int SP_WAVES = 8>
-static hipError_t launch_sparse(SparseArgs a, bool compact, hipStream_t stream)
+static hipError_t launch_sparse(SparseArgs a, bool compact, int n_seq, hipStream_t stream)
 {
     a.npass = (a.ntiles + SP_WAVES * TPW - 1) / (SP_WAVES * TPW);
     a.tpp = (a.ntiles + a.npass - 1) / a.npass;
-    dim3 grid(a.Hkv, ((a.R + 15) / 16) * DS), block(SP_WAVES * 64);
-    if (compact) hipLaunchKernelGGL((sparse_bf16_kernel<D, DS, TPW, SP_WAVES, true>), grid, block, 0, stream, a);
-    else hipLaunchKernelGGL((sparse_bf16_kernel<D, DS, TPW, SP_WAVES, false>), grid, block, 0, stream, a);
+    dim3 grid(n_seq * a.Hkv, ((a.R + 15) / 16) * DS), block(SP_WAVES * 64);
+    if (compact) hipLaunchKernelGGL((sparse_bf16_kernel<D, DS, TPW, SP_WAVES, SP_COMPACT>), grid, block, 0, stream, a);
+    else if (n_seq > 1) hipLaunchKernelGGL((sparse_bf16_kernel<D, DS, TPW, SP_WAVES, SP_SEQS>), grid, block, 0, stream, a);
+    else hipLaunchKernelGGL((sparse_bf16_kernel<D, DS, TPW, SP_WAVES, SP_GATHER>), grid, block, 0, stream, a);
     return hipGetLastError();
 }
 
@@ -451,25 +460,36 @@ static hipError_t launch_sparse(SparseArgs a, bool compact, hipStream_t stream)
 // k = 700 8.6 us in two passes of eight, 7.0 in one of sixteen with three tiles each, k = 900 8.6 and 7.9 with four; where they
 // do not, eight are faster (k = 1000: 8.6 against 9.7 us in two passes of sixteen with three).  Nine tiles per wavefront instead of two passes of five are hardly faster (k = 1000: 8.8 against 9.0 us).
 template <int D, int DS>
-static hipError_t launch_sparse_any(const SparseArgs &a, bool compact, hipStream_t stream)
+static hipError_t launch_sparse_any(const SparseArgs &a, bool compact, int n_seq, hipStream_t stream)
 {
     constexpr int SP_WAVES = 8;
     if constexpr (D / DS <= 32) {
-        if ((a.ntiles > 40 && a.ntiles <= 48) || (a.ntiles > 80 && a.ntiles <= 96)) return launch_sparse<D, DS, 3, 16>(a, compact, stream);
+        if ((a.ntiles > 40 && a.ntiles <= 48) || (a.ntiles > 80 && a.ntiles <= 96)) return launch_sparse<D, DS, 3, 16>(a, compact, n_seq, stream);
         if constexpr (D == 128)
-            if (a.ntiles > 48 && a.ntiles <= 64) return launch_sparse<D, DS, 4, 16>(a, compact, stream);
+            if (a.ntiles > 48 && a.ntiles <= 64) return launch_sparse<D, DS, 4, 16>(a, compact, n_seq, stream);
         if constexpr (D == 64)
-            if (a.ntiles > 48 && a.ntiles <= 80) return launch_sparse<D, DS, 5, 16>(a, compact, stream);
+            if (a.ntiles > 48 && a.ntiles <= 80) return launch_sparse<D, DS, 5, 16>(a, compact, n_seq, stream);
     }
-    if (a.ntiles <= SP_WAVES) return launch_sparse<D, DS, 1>(a, compact, stream);
-    if (a.ntiles <= 2 * SP_WAVES) return launch_sparse<D, DS, 2>(a, compact, stream);
-    if (a.ntiles <= 3 * SP_WAVES) return launch_sparse<D, DS, 3>(a, compact, stream);
-    return launch_sparse<D, DS, 5>(a, compact, stream);
+    if (a.ntiles <= SP_WAVES) return launch_sparse<D, DS, 1>(a, compact, n_seq, stream);
+    if (a.ntiles <= 2 * SP_WAVES) return launch_sparse<D, DS, 2>(a, compact, n_seq, stream);
+    if (a.ntiles <= 3 * SP_WAVES) return launch_sparse<D, DS, 3>(a, compact, n_seq, stream);
+    return launch_sparse<D, DS, 5>(a, compact, n_seq, stream);
+}
+
+// Batched call: does this kernel take it?  While every (unit = sequence and KV head, 16-row tile) has a compute unit of its own, its
+// split of the channels and whole passes in flight beat the kernels that share a unit's rows (28 heads in 4 groups, B = 32, k = 300:
+// 2 sequences 7.3 -> 5.7 us, 4 sequences 7.5 -> 6.8; 32 heads in 8, B = 8: 2 sequences 7.0 -> 4.9 us, 12 sequences 8.4 -> 7.1).  A chip
+// full of units with many keys each is bound by the gather, which sparse_batch_kernel's stream of requests uses better (256
+// units, k = 1000: 27.1 against 27.6 us).  Units vary fastest over the grid, so that those of a call with a multiple of
+// eight have their workgroups on one XCD (2 KV heads, B = 4, k = 1000, 32 sequences: 12.7 us with sequences slowest, 7.5 so).
+bool sparse_takes_sequences(long long n_units, int R, long long n_keys)
+{
+    return n_units * ((R + 15) / 16) <= kBf16Workgroups && (n_units < kBf16Workgroups || n_keys <= 512);
 }
 
 // The output channels are split over as many workgroups (1, 2 or 4 per row tile) as still leaves
 // every workgroup a compute unit of its own.
-hipError_t bf16_sparse(const KernelArgs &k, int d, bool compact, hipStream_t stream)
+hipError_t bf16_sparse(const KernelArgs &k, int d, bool compact, int n_seq, hipStream_t stream)
 {
     if (k.nc <= 0 || k.nc > 0x7fffffff - k.n_blk || k.R <= 0 || (long long)k.R * k.B >= (1ll << 32) ||
         (long long)k.Hkv * d * 2 >= (1ll << 31))
@@ -482,16 +502,18 @@ hipError_t bf16_sparse(const KernelArgs &k, int d, bool compact, hipStream_t str
     a.ntiles = (a.nc + a.n_blk + SP_KT - 1) / SP_KT;
     a.inv_B = k.B >= 2 ? (unsigned)(((1ull << 32) + k.B - 1) / k.B) : 0u;
     a.scale_log2 = k.scale_log2;
-    const long long wgs = (long long)a.Hkv * ((a.R + 15) / 16);
+    a.seq_q = k.seq_q; a.seq_kv = k.seq_kv; a.seq_idx = k.seq_idx; a.seq_blk = k.seq_blk; a.seq_out = k.seq_out; a.seq_lse = k.seq_lse;
+    a.inv_Hkv = k.Hkv >= 2 ? (unsigned)(((1ull << 32) + k.Hkv - 1) / k.Hkv) : 0u;
+    const long long wgs = (long long)n_seq * a.Hkv * ((a.R + 15) / 16);
     const int ds = 4 * wgs <= kBf16Workgroups ? 4 : 2 * wgs <= kBf16Workgroups ? 2 : 1;
     if (d == 128) {
-        if (ds == 4) return launch_sparse_any<128, 4>(a, compact, stream);
-        if (ds == 2) return launch_sparse_any<128, 2>(a, compact, stream);
-        return launch_sparse_any<128, 1>(a, compact, stream);
+        if (ds == 4) return launch_sparse_any<128, 4>(a, compact, n_seq, stream);
+        if (ds == 2) return launch_sparse_any<128, 2>(a, compact, n_seq, stream);
+        return launch_sparse_any<128, 1>(a, compact, n_seq, stream);
     }
     if (d == 64) {
-        if (ds >= 2) return launch_sparse_any<64, 2>(a, compact, stream);
-        return launch_sparse_any<64, 1>(a, compact, stream);
+        if (ds >= 2) return launch_sparse_any<64, 2>(a, compact, n_seq, stream);
+        return launch_sparse_any<64, 1>(a, compact, n_seq, stream);
     }
     return hipErrorInvalidValue;
 }

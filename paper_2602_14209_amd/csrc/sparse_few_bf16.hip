@@ -6,9 +6,10 @@
 // parts: every iteration takes KP tiles, one per key part, so the chain is KP times shorter, and there are 8 / RW times as
 // many workgroups.  The price is that every workgroup of a unit fetches the unit's rows (from the XCD's L2, which the row
 // groups of a unit share) and that the key parts are merged through LDS at the end.  The ring takes 136 KB, one
-// workgroup per CU: this kernel is for calls that leave CUs idle (sparse_few_row_tiles).
+// workgroup per CU: this kernel is for calls that leave CUs idle (sparse_few_row_tiles); the smallest calls go to
+// sparse_bf16.hip, one 16-row tile per workgroup (sparse_takes_sequences).
 // Measured at 28 query heads in 4 groups, B = 32, k = 300: 12 sequences 14.7 us with 128-row workgroups (96 of them), 11.7 us
-// with 64-row ones (192); 2 sequences 13.7 us with 4, 7.1 us with 112 of 16 rows.  16 sequences with B = 8, k = 1000: 24.2 -> 14.5 us.
+// with 64-row ones (192).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -298,7 +299,8 @@ void sparse_few_kernel(const BatchArgs a)
     if (a.lse_out && kp == 0 && lg4 == 0) a.lse_out[z * a.seq_lse + orow] = (M + log2f(lt)) * 0.6931471805599453f;
 }
 
-// As few row tiles per workgroup as still give every workgroup a compute unit of its own (ids come in blocks of 8 units).
+// As few row tiles per workgroup, two or four, as still give every workgroup a compute unit of its own (ids come in blocks of 8
+// units; calls that could have one are sparse_bf16.hip's).
 // (With 320 .. 512 workgroups of 4 row tiles and a ring of half the size, two per CU: 32 heads, k = 300, 24 sequences 17.8 us
 // against 16.4 with 128-row workgroups; no gain.)  Units that fill the chip one each anyway and are long are bound by
 // the gather's bandwidth, which the other kernel's continuous stream of requests uses better than whole iterations at a
@@ -307,7 +309,7 @@ int sparse_few_row_tiles(long long n_units, int R, int n_keys)
 {
     const long long ids = (n_units + 7) / 8 * 8;
     if (ids * ((R + 127) / 128) >= 256 && n_keys > 512) return 0;
-    for (int rw = 1; rw <= 4; rw *= 2)
+    for (int rw = 2; rw <= 4; rw *= 2)
         if (ids * ((R + 16 * rw - 1) / (16 * rw)) <= 256) return rw;
     return 0;
 }
@@ -317,8 +319,7 @@ static hipError_t launch_few(const BatchArgs &a, int row_tiles, hipStream_t stre
 {
     const int row_groups = (a.R + 16 * row_tiles - 1) / (16 * row_tiles);
     dim3 grid(8 * row_groups, (a.n_units + 7) / 8), block(SB_WAVES * 64);
-    if (row_tiles == 1) hipLaunchKernelGGL((sparse_few_kernel<D, 1>), grid, block, 0, stream, a);
-    else if (row_tiles == 2) hipLaunchKernelGGL((sparse_few_kernel<D, 2>), grid, block, 0, stream, a);
+    if (row_tiles == 2) hipLaunchKernelGGL((sparse_few_kernel<D, 2>), grid, block, 0, stream, a);
     else if (row_tiles == 4) hipLaunchKernelGGL((sparse_few_kernel<D, 4>), grid, block, 0, stream, a);
     else return hipErrorInvalidValue;
     return hipGetLastError();

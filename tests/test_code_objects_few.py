@@ -4,7 +4,7 @@ from test_code_objects import _code_object, _demangle, _early_uses, _sgpr_hazard
 
 def test_few_sequences_kernels(tmp_path):
     meta, kernels = _code_object(str(tmp_path), "sparse_few_bf16")
-    assert len(meta) == 6
+    assert len(meta) == 4
     for sym, m in meta.items():
         name, ins = _demangle(sym), kernels[sym]
         assert m["scratch"] == 0 and m["vspill"] == 0 and m["vgpr"] + m["agpr"] <= 256 and m["lds"] <= 160 * 1024, (name, m)

@@ -1,5 +1,6 @@
-"""Batched sparse step with few sequences: one, two and four row tiles per workgroup (eight, four and two key parts), last
-iterations that leave key parts without a tile, fewer tiles than key parts, index windows that are refilled."""
+"""Batched sparse step with few sequences: two and four row tiles per workgroup (four and two key parts), last
+iterations that leave key parts without a tile, fewer tiles than key parts, index windows that are refilled; and fewer still, which the single-sequence kernel takes with a sequence dimension (channels in
+four, two parts and unsplit, one and more passes)."""
 import zlib
 
 import numpy as np
@@ -20,6 +21,13 @@ pytestmark = pytest.mark.gpu
     ("f6", 12, 28, 4, 128, 700, 31, 301),    # four row tiles, the last one of a unit half empty
     ("f7", 9, 32, 8, 64, 2400, 16, 2200),    # d = 64, refilled windows, two row tiles
     ("f8", 32, 8, 8, 128, 300, 3, 100),      # 256 units of three rows
+    ("f9", 32, 8, 8, 128, 700, 3, 600),      # the same with more keys: the kernel for many units
+    ("s1", 3, 3, 1, 128, 900, 7, 633),       # one KV head; channels in four parts, one full pass
+    ("s2", 5, 6, 3, 64, 1100, 8, 1016),      # 15 units of one row tile, two channel parts, sixteen wavefronts
+    ("s3", 9, 14, 2, 128, 700, 16, 300),     # 18 units x 7 row tiles: two channel parts
+    ("s4", 6, 40, 5, 128, 800, 16, 700),     # 30 units x 8 row tiles: channels unsplit, two passes
+    ("s5", 30, 8, 8, 64, 300, 5, 120),       # 240 units
+    ("s6", 4, 16, 8, 128, 1500, 9, 1015),    # 32 units x 2 row tiles, four channel parts, sixteen wavefronts of four tiles
 ])
 def test_few_sequences(oracle_mod, case):
     import torch
