@@ -552,7 +552,10 @@ void attn_bf16_kernel(const KernelArgs a)
                 mx = fmaxf(lo, hi) * a.scale_log2;
             }
             if (__any(mx > m_run + kLazy)) {      // uniform: some row's maximum has run ahead of its reference
-                const float m_new = fmaxf(m_run, ceilf(mx));        // whole numbers: the split merges scale by exact powers of two
+                // The statistics' references are whole numbers: the fp64 merge of the splits scales by exact powers of two.
+                // Attention follows the maximum itself, so that a key that dominates its row keeps a probability of 1, which
+                // bf16 holds exactly.
+                const float m_new = fmaxf(m_run, WITH_V ? mx : ceilf(mx));
                 const float corr = __builtin_amdgcn_exp2f(m_run - m_new);
                 m_run = m_new;
                 l_run *= corr;
@@ -688,8 +691,9 @@ void attn_bf16_kernel(const KernelArgs a)
     if (WITH_V && a.stat_m != nullptr) {
         if (owner && row < a.R && lg == 0) {
             const long long pi = ((long long)h * a.n_split + split) * a.rpad + row;
-            a.stat_m[pi] = m_pre;
-            a.stat_l[pi] = lp_tot;
+            const float whole = ceilf(m_pre);              // as the statistics pass leaves them
+            a.stat_m[pi] = whole;
+            a.stat_l[pi] = lp_tot * __builtin_amdgcn_exp2f(m_pre - whole);
         }
     }
 

@@ -152,7 +152,7 @@ __global__ __launch_bounds__(kF32Waves * 64) __attribute__((amdgpu_waves_per_eu(
         mx = fmaxf(mx, __shfl_xor(mx, 16));
         mx = fmaxf(mx, __shfl_xor(mx, 32)) * a.scale_log2;
         if (__any(mx > m_run + kLazy)) {
-            const float m_new = fmaxf(m_run, ceilf(mx));        // whole numbers: the split merges scale by exact powers of two
+            const float m_new = fmaxf(m_run, ceilf(mx));        // whole numbers: the fp64 split merge of near-ties scales by exact powers of two
             const float corr = exp2f(m_run - m_new);
             m_run = m_new;
             l_run *= corr;
